@@ -1081,6 +1081,7 @@ int fdi_forward_steps(fd_grid *g, const fd_shot *sh, int nt, int n0, int n1, flo
         a.inj = make_inject(g, 0, sh->src_wavelet + (size_t)n * sh->nsrc, inj_scale);
         a.smp = make_sample(g, 1, sh->nrec, row(n - 1), smp_scale);
         a.nsamp_blocks = samp_blocks(a.smp);
+        a.flip = n & 1;
         HIPCHK(launch_step(a, g->st, g->diff ? kDiff : kPlain, s));
         g->rows_done = std::max(g->rows_done, std::min(n, nt));
         std::swap(g->cur, g->prev);
@@ -1196,6 +1197,7 @@ extern "C" int fd_adjoint(fd_grid *g, const fd_shot *sh, int nt, double dt,
         a.inj = make_inject(g, 1, residual + (size_t)(k - 1) * sh->nrec, inj_scale);
         a.smp = make_sample(g, 0, sh->nsrc, k <= nt - 1 ? src_adj + (size_t)k * sh->nsrc : nullptr, smp_scale);
         a.nsamp_blocks = samp_blocks(a.smp);
+        a.flip = k & 1;
         HIPCHK(launch_step(a, g->st, kPlain, s));
         std::swap(A, B);
     }
@@ -1312,6 +1314,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         a.nsamp_blocks = samp_blocks(a.smp);
         a.img = Imaging{};
         a.img.br_out = brf;
+        a.flip = n & 1;
         a.ntz = g->ntz[kBracket];
         a.zchunk = g->zchunk[kBracket];
         HIPCHK(launch_step(a, g->st, kBracket, s));
@@ -1334,6 +1337,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         a.img = Imaging{};
         a.img.br_in = brf;
         a.img.gpart = gpart;
+        a.flip = k & 1;
         a.ntz = g->ntz[kImage];
         a.zchunk = g->zchunk[kImage];
         HIPCHK(launch_step(a, g->st, kImage, s));
@@ -1475,6 +1479,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
                                             (act.first && n >= 1) ? recb + (size_t)(n - 1) * sh->nrec : nullptr, 1.f);
                         a.nsamp_blocks = samp_blocks(a.smp);
                         a.img = Imaging{};
+                        a.flip = n & 1;
                         a.ntz = g->ntz[kPlain];
                         a.zchunk = g->zchunk[kPlain];
                         HIPCHK(launch_step(a, g->st, kPlain, s));

@@ -325,8 +325,14 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
     // Odd chunks march downwards: two adjacent chunks then read the warm-up
     // planes around their common boundary at about the same time (both at
     // their start, or both at their end), while the first read is still
-    // cached.  Measured: 0.5 % fewer fetched bytes, 0.5-1 % faster.
-    const int dir = (bz & 1) ? -1 : 1;
+    // cached.  Measured: 0.5 % fewer fetched bytes, 0.5-1 % faster.  Every
+    // other step reverses the whole pattern (a.flip): a step then starts on
+    // the planes its predecessor touched last, part of which the memory-side
+    // cache (256 MB) still holds.  Measured per step at so 8, float32: 416^3
+    // 203 -> 191 us, 512^3 383 -> 363, 592^3 692 -> 671; bfloat16 with p
+    // codes 512^3 234 -> 220, 592^3 393 -> 382; grids whose fields fit that
+    // cache (up to 336^3) are unchanged.
+    const int dir = ((bz ^ a.flip) & 1) ? -1 : 1;
     const int len = z1 - z0;
     const int zs = dir > 0 ? z0 : z1 - 1;   // first plane of the march
 
