@@ -670,7 +670,8 @@ int ensure_side(fd_grid *g, int side, int npts, const double *xyz, hipStream_t s
 
 StepArgs base_args(const fd_grid *g) {
     StepArgs a{};
-    a.L = g->L;
+    const Layout &L = g->L;
+    a.L = L;
     a.p = g->p;
     a.pq = g->pq;
     a.pq_base = g->pq_base;
@@ -707,6 +708,14 @@ StepArgs base_args(const fd_grid *g) {
     // and 7 % at 280^3 (the written lines crowd out of L2 the neighbour rows
     // that the halo loads expect there).
     a.out_cached = (g->st != Store::F32 && g->wp.field_bytes <= kCachedField) ? 1 : 0;
+    // Float32 p of up to kCachedField bytes is read with ordinary loads, so
+    // that what of it the memory-side cache keeps from the step before is not
+    // fetched again.  Measured at so 8 (us per step, non-temporal -> ordinary):
+    // float32 224^3 33.7 -> 31.6, 272^3 59.5 -> 55.6, 320^3 (131 MB of p) 80.8
+    // -> 77.5, 336^3 101.4 -> 100.9, 416^3 191 -> 198; bfloat16 272^3 43.4 ->
+    // 41.0, 336^3 72.8 -> 73.8, 416^3 130 -> 135.  Codes of p show no
+    // difference at any size and stay non-temporal.
+    a.p_cached = (size_t)L.nx * L.ny * L.nz * sizeof(float) <= kCachedField;
     a.ntz = g->ntz[kPlain];
     a.zchunk = g->zchunk[kPlain];
     return a;

@@ -125,6 +125,7 @@ struct StepArgs {
     int shape3;             // 3D tile shape code: 16, 8 or kShapeMixed
     int nstrip;             // mixed shape: 32 x 32 tiles of the last x column (else 0)
     int out_cached;         // 3D: store u^{n+1} with an ordinary store, not a non-temporal one
+    int p_cached;           // 3D: read float32 p with ordinary loads, not non-temporal ones
     int zchunk;             // planes per 3D workgroup
     int flip;               // 3D: 1 reverses the z march of every chunk (alternates from step to step)
     int nsamp_blocks;       // trailing workgroups that sample instead of stepping

@@ -464,6 +464,8 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
         for (int k = 0; k < HPT; ++k) r.hv[k] = E::ld4raw(U + hoff[k] + fo);
         if constexpr (PQ)
             r.pv = ld2nt_u32(Pq + base + zo);
+        else if (a.p_cached)
+            r.pv = *reinterpret_cast<const float4 *>(Pp + base + zo);
         else
             r.pv = ld4nt_f32(Pp + base + zo);
         r.mv = E::ld4ntraw(Pv + base + zo);
