@@ -27,6 +27,7 @@
 
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -784,23 +785,79 @@ __global__ void k_fill_velocity(const Layout L, const float *vp, int vp_padded, 
     }
 }
 
-__global__ void k_vrange(const Layout L, const float *vel, unsigned *out) {
-    const long long n = (long long)L.nx * L.ny * L.nz;
-    float m = 0.f, lo = __uint_as_float(0x7F800000u);
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % L.nx);
-        const int y = (int)((i / L.nx) % L.ny);
-        const int z = (int)(i / ((long long)L.nx * L.ny));
-        const float v = vel[L.offset(x, y, z)];
-        // NaN or non-positive velocities poison the maximum on purpose
-        m = (v > 0.f) ? fmaxf(m, v) : __uint_as_float(0x7F800000u);
-        if (!(v > 0.f)) break;
-        lo = fminf(lo, v);
+// Grid-stride walk over the float4 groups of a field's grid rows: a lane
+// takes 4 consecutive points at a time (the last group of a row may reach
+// past nx), so one index division serves 4 points and the pitched side of
+// every access is one 16-byte access per lane.
+struct Quads {
+    const Layout &L;
+    const int g4;          // groups per row
+    const long long n, step;
+    long long i;
+    int gx, y, z;
+    __device__ explicit Quads(const Layout &l)
+        : L(l), g4((l.nx + 3) / 4), n((long long)((l.nx + 3) / 4) * l.ny * l.nz),
+          step((long long)gridDim.x * blockDim.x), i((long long)blockIdx.x * blockDim.x + threadIdx.x) {
+        split();
     }
-    // positive floats order as their bit patterns
-    atomicMax(out, __float_as_uint(m));
-    atomicMin(out + 1, __float_as_uint(lo));
+    __device__ void split() {
+        if (n < (1LL << 31)) {   // (32-bit division is several times cheaper)
+            const unsigned row = (unsigned)i / (unsigned)g4;
+            gx = (int)((unsigned)i - row * (unsigned)g4);
+            z = (int)(row / (unsigned)L.ny);
+            y = (int)(row - (unsigned)z * (unsigned)L.ny);
+        } else {
+            const long long row = i / g4;
+            gx = (int)(i - row * g4);
+            z = (int)(row / L.ny);
+            y = (int)(row - (long long)z * L.ny);
+        }
+    }
+    __device__ bool more() const { return i < n; }
+    __device__ void next() {
+        i += step;
+        if (i < n) split();
+    }
+    __device__ int x() const { return 4 * gx; }
+    __device__ long long offset() const { return L.offset(4 * gx, y, z); }   // a multiple of 4
+};
+
+// Two atomics per workgroup: the lanes' extremes are reduced in the wave and
+// then through LDS.  (With two atomics per lane, four million on two
+// addresses at most, the kernel took 750 us on any grid of more than 2 M
+// points, whatever its size: the atomics were the bound.)
+__global__ __launch_bounds__(kBlock) void k_vrange(const Layout L, const float *vel, unsigned *out) {
+    float m = 0.f, lo = __uint_as_float(0x7F800000u);
+    for (Quads q(L); q.more(); q.next()) {
+        const float4 v4 = *reinterpret_cast<const float4 *>(vel + q.offset());
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = comp(v4, i);
+            if (q.x() + i >= L.nx) break;
+            // NaN or non-positive velocities poison the maximum on purpose
+            m = (v > 0.f) ? fmaxf(m, v) : __uint_as_float(0x7F800000u);
+            lo = (v > 0.f) ? fminf(lo, v) : lo;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, o, 64));
+        lo = fminf(lo, __shfl_xor(lo, o, 64));
+    }
+    __shared__ float s_m[kBlock / 64], s_lo[kBlock / 64];
+    if (threadIdx.x % 64 == 0) {
+        s_m[threadIdx.x / 64] = m;
+        s_lo[threadIdx.x / 64] = lo;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w) {
+            m = fmaxf(m, s_m[w]);
+            lo = fminf(lo, s_lo[w]);
+        }
+        // positive floats order as their bit patterns
+        atomicMax(out, __float_as_uint(m));
+        atomicMin(out + 1, __float_as_uint(lo));
+    }
 }
 
 __global__ void k_make_p(const Layout L, const float *vel, double dt2, float *p) {
@@ -1022,8 +1079,8 @@ hipError_t launch_fill_velocity(const Layout &L, const float *vp, int vp_padded,
 }
 
 hipError_t launch_vrange(const Layout &L, const float *vel, unsigned *out_bits, hipStream_t s) {
-    const long long n = (long long)L.nx * L.ny * L.nz;
-    hipLaunchKernelGGL(k_vrange, dim3(grid_for(n)), dim3(kBlock), 0, s, L, vel, out_bits);
+    const long long quads = (long long)((L.nx + 3) / 4) * L.ny * L.nz;
+    hipLaunchKernelGGL(k_vrange, dim3(std::min(2048, grid_for(quads))), dim3(kBlock), 0, s, L, vel, out_bits);
     return hipGetLastError();
 }
 
