@@ -144,8 +144,14 @@ typedef struct fd_grid_desc {
                               workspace); 0 selects automatically (two levels at space
                               order 2 in 3D float32, measured 11-12 % faster there; one
                               step elsewhere, where the recomputed ring of the two-level
-                              kernel costs more than the traffic it saves); anything
-                              else, or 2 where it is not available, is FD_ERR_ARG */
+                              kernel costs more than the traffic it saves; 2D grids of up
+                              to 1 GiB per field run up to 8 levels per launch, chosen by
+                              radius and grid size, in fd_forward, fd_adjoint and
+                              fd_gradient's fixed-interval schedules, with two more
+                              wavefield buffers and 2 (levels - 2) scratch ones in the
+                              workspace; results are bitwise those of 1); anything
+                              else, or 2 where it is not available, is FD_ERR_ARG.
+                              Served 2D shots run one step per launch */
     int param_storage;     /* fd_param_storage; FD_PARAM_Q16 in 3D only */
 } fd_grid_desc;
 
@@ -183,7 +189,7 @@ typedef struct fd_grid_info {
     int tile_strip;        /* 3D: width of the last x column when it runs 32 x 32 tiles
                               beside 64 x 16 ones, else 0 */
     int zchunk;            /* 3D: z planes per workgroup of a plain step; 2D: 64 */
-    int time_block;        /* steps per launch of fd_forward (1 or 2) */
+    int time_block;        /* steps per launch of fd_forward (3D: 1 or 2; 2D: 1 to 8) */
     int param_storage;     /* fd_param_storage in use */
     double param_base;     /* FD_PARAM_Q16: p0 and dp of the latest dt (float32 values), */
     double param_step;     /* 0 before the first call that steps or with FD_PARAM_F32 */
@@ -260,7 +266,8 @@ int fd_adjoint(fd_grid *grid, const fd_shot *shot, int nt, double dt,
 /* Device workspace for fd_gradient.  Default: checkpoints of (u^c, u^{c-1})
  * every checkpoint_every steps except the last segment's (ceil(nt /
  * checkpoint_every) - 1 pairs) and checkpoint_every bracket fields of the
- * segment recompute; with checkpoint_every >= nt, nt bracket fields and no
+ * segment recompute (and two more fields on 2D grids that run several levels
+ * per launch); with checkpoint_every >= nt, nt bracket fields and no
  * checkpoint (the forward pass keeps every bracket, nothing is recomputed).
  * FD_GRAD_BINOMIAL: checkpoint_every + 1 snapshots and two scratch fields.
  * All add the float64 gradient, its float32 partial sum, traces and

@@ -170,6 +170,7 @@ struct SparseDev {   // device tables of one side (sources or receivers)
 
 struct WsPlan {
     size_t vel, p, uA, uB, uC, uD, damp, misc, total;
+    size_t scr;              // 2D: scratch fields of the several-level step
     size_t t2pp, t2corner;   // extended source tables of the two-level step (0 when unused)
     size_t stage_t2;         // their host staging area
     size_t src[6], rec[6];   // idx, w, plane_ptr, corner, ent_src, ent_w
@@ -230,6 +231,21 @@ bool t2_enabled(const fd_grid_desc *d) {
                        d->param_storage == FD_PARAM_F32;
     return avail && (d->time_block == 2 || (d->time_block == 0 && d->space_order == 2));
 }
+
+// Levels per launch of a 2D grid's forward, adjoint and gradient steps
+// (k_step2d_tb; 0: one step per launch, k_step2d).  The automatic choice;
+// time_block 1 asks for one step per launch.  The levels need two more state
+// fields and, beyond two levels, scratch fields for the sampled levels, so
+// grids of more than kTb2MaxField bytes per field keep two fields.
+constexpr size_t kTb2MaxField = size_t(1) << 30;
+int tb2_levels(const fd_grid_desc *d, const Layout &L) {
+    if (d->ndim != 2 || d->time_block != 0) return 0;
+    if ((size_t)L.elems * (d->storage == FD_STORE_F32 ? 4 : 2) > kTb2MaxField) return 0;
+    return step2d_levels(L);
+}
+// Scratch fields of those levels: the levels a launch neither starts from nor
+// ends with, twice (a launch samples those of the one before it).
+inline int tb2_scratch(int levels) { return levels > 2 ? 2 * (levels - 2) : 0; }
 
 // 16-bit value-and-difference storage, and the element type of a storage.
 inline bool diff_storage(const fd_grid_desc *d) {
@@ -298,8 +314,10 @@ WsPlan plan(const fd_grid_desc *d, const Layout &L) {
     w.uA = o; o += w.field_bytes;
     w.uB = o; o += w.field_bytes;
     const bool t2 = t2_enabled(d);
-    w.uC = o; if (t2 || diff_storage(d)) o += w.field_bytes;   // (the difference field)
-    w.uD = o; if (t2) o += w.field_bytes;
+    const int tb2 = tb2_levels(d, L);
+    w.uC = o; if (t2 || tb2 || diff_storage(d)) o += w.field_bytes;   // (the difference field)
+    w.uD = o; if (t2 || tb2) o += w.field_bytes;
+    w.scr = o; o += w.field_bytes * (size_t)tb2_scratch(tb2);
     w.damp = o; o = align_up(o + sizeof(float) * (size_t)(L.nx + L.ny + L.nz), 256);
     w.misc = o; o = align_up(o + sizeof(double) * kNPart + 256, 256);
     o += side_bytes(w.cap_src, nc, nptr, w.src, o);
@@ -350,6 +368,7 @@ struct fd_grid {
     std::vector<double> cached_xyz[2];
     int cached_n[2];
     int ncorner[2];        // injection corners in the current tables
+    int one_entry[2];      // each of them has a single entry
     double vmax, vmin, dt_crit, sigma_max;
     double dt_cached;
     char *stage;
@@ -370,6 +389,7 @@ struct fd_grid {
     bool t2;
     void *uC, *uD;
     bool diff;               // 16-bit value and difference: the difference lives in uC
+    int tb2;                 // 2D: levels per launch (0: one step per launch)
     int t2_ntz, t2_zchunk;
     int *t2_pp;
     int4 *t2_corner;
@@ -585,7 +605,8 @@ int ensure_side(fd_grid *g, int side, int npts, const double *xyz, hipStream_t s
             ew.push_back(ents[j].w);
             ++j;
         }
-        corners.push_back(make_int4(ents[i].x, ents[i].y, beg, (int)esrc.size()));
+        // (2D kernels take z in the second place)
+        corners.push_back(make_int4(ents[i].x, ndim == 3 ? ents[i].y : ents[i].z, beg, (int)esrc.size()));
         ckey.push_back((long long)ents[i].tile * (L.nz + 1) + ents[i].z);
         i = j;
     }
@@ -665,6 +686,7 @@ int ensure_side(fd_grid *g, int side, int npts, const double *xyz, hipStream_t s
     g->cached_xyz[side] = std::move(key);
     g->cached_n[side] = npts;
     g->ncorner[side] = (int)corners.size();
+    g->one_entry[side] = corners.size() == esrc.size();
     return FD_OK;
 }
 
@@ -749,6 +771,104 @@ Sample make_sample(const fd_grid *g, int side, int npts, float *out, float scale
 
 inline int samp_blocks(const Sample &s) { return sample_blocks(s); }
 
+// A 2D run of several levels per launch.  The state (u^n in cur, u^{n-1} in
+// prev) rotates through four fields, and the rows sampled from a launch's
+// levels are written by the next launch's trailing workgroups or by flush().
+class Tb2Run {
+public:
+    Tb2Run(fd_grid *g, int mode, void *const fields[4], void *cur_, void *prev_, int inj_side, float inj_scale,
+           int smp_side, int npts, float smp_scale, hipStream_t s)
+        : cur(cur_), prev(prev_), g_(g), mode_(mode), inj_(inj_side), smp_(smp_side), npts_(npts),
+          inj_scale_(inj_scale), smp_scale_(smp_scale), s_(s), base_(base_args(g)) {
+        for (int i = 0; i < 4; ++i) fields_[i] = fields[i];
+    }
+    void *cur, *prev;
+    // Advance nlev levels.  Level t takes the injected row vals + t * vstride
+    // and gives the sampled row out + t * ostride (vals, out null: none);
+    // br[t] is its bracket (gradient modes).
+    int advance(int nlev, const float *vals, long long vstride, float *out, long long ostride,
+                float *const *br, float *gpart) {
+        void *f[2] = {nullptr, nullptr};   // the fields not holding the state
+        for (void *b : fields_)
+            if (b != cur && b != prev) (f[0] ? f[1] : f[0]) = b;
+        Step2Args a{};
+        a.L = g_->L;
+        a.u = cur;
+        a.prev = prev;
+        a.out = f[0];
+        a.outp = f[1];
+        a.p = g_->p;
+        a.damp = g_->damp;
+        a.w0 = base_.w0;
+        for (int j = 0; j <= kMaxR; ++j) {
+            a.wx[j] = base_.wx[j];
+            a.wz[j] = base_.wz[j];
+        }
+        a.nlev = nlev;
+        const SparseDev &d = g_->sd[inj_];
+        a.inj_pp = d.plane_ptr;
+        a.corner = d.corner;
+        a.src = d.ent_src;
+        a.w = d.ent_w;
+        a.vals = g_->ncorner[inj_] > 0 ? vals : nullptr;
+        a.vstride = vstride;
+        a.scale = inj_scale_;
+        a.one_entry = g_->one_entry[inj_];
+        a.smp = pend_;
+        a.nsamp_blocks = pend_.nrows * pend_.bpr;
+        const bool smp = out && npts_ > 0;
+        a.node_pp = smp ? g_->sd[smp_].plane_ptr : nullptr;
+        SampleRows next{};
+        for (int t = 0; t < nlev; ++t) {
+            void *lev = t == nlev - 1   ? f[0]
+                        : t == nlev - 2 ? f[1]
+                                        : g_->ws + g_->wp.scr + g_->wp.field_bytes * (size_t)(par_ * (g_->tb2 - 2) + t);
+            a.lev_out[t] = lev;
+            next.field[t] = lev;
+            if (mode_ == kBracket) a.br_out[t] = br[t];
+            if (mode_ == kImage) a.br_in[t] = br[t];
+        }
+        a.gpart = gpart;
+        HIPCHK(launch_step2d_tb(a, g_->st, mode_, s_));
+        if (smp) {
+            const Sample q = make_sample(g_, smp_, npts_, out, smp_scale_);
+            next.npts = npts_;
+            next.nc = q.nc;
+            next.lpp = q.lpp;
+            next.nrows = nlev;
+            next.bpr = sample_rows_blocks(npts_, q.lpp);
+            next.idx = q.idx;
+            next.w = q.w;
+            next.out = out;
+            next.ostride = ostride;
+            next.scale = smp_scale_;
+            pend_ = next;
+        } else {
+            pend_ = SampleRows{};
+        }
+        prev = nlev > 1 ? f[1] : cur;
+        cur = f[0];
+        par_ ^= 1;
+        return FD_OK;
+    }
+    // Write the rows still pending.
+    int flush() {
+        HIPCHK(launch_sample_rows(pend_, g_->st, s_));
+        pend_ = SampleRows{};
+        return FD_OK;
+    }
+
+private:
+    fd_grid *g_;
+    int mode_, inj_, smp_, npts_;
+    float inj_scale_, smp_scale_;
+    hipStream_t s_;
+    StepArgs base_;
+    void *fields_[4];
+    SampleRows pend_{};
+    int par_ = 0;
+};
+
 int check_dt(const fd_grid *g, double dt, int nt) {
     if (nt < 0) return fdi_fail(FD_ERR_ARG, "nt < 0");
     if (!(dt > 0.0) || !std::isfinite(dt)) return fdi_fail(FD_ERR_ARG, "dt must be > 0");
@@ -816,6 +936,7 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
     g->uA = g->ws + wp.uA;
     g->uB = g->ws + wp.uB;
     g->t2 = t2_enabled(desc);
+    g->tb2 = tb2_levels(desc, L);
     g->uC = g->ws + wp.uC;
     g->uD = g->ws + wp.uD;
     g->t2_pp = (int *)(g->ws + wp.t2pp);
@@ -937,12 +1058,15 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
     hipError_t e = hipSuccess;
     if ((e = launch_zero_field(L, g->uA, g->st, s)) != hipSuccess ||
         (e = launch_zero_field(L, g->uB, g->st, s)) != hipSuccess ||
-        ((g->t2 || g->diff) && (e = launch_zero_field(L, g->uC, g->st, s)) != hipSuccess) ||
-        (g->t2 && (e = launch_zero_field(L, g->uD, g->st, s)) != hipSuccess) ||
+        ((g->t2 || g->tb2 || g->diff) && (e = launch_zero_field(L, g->uC, g->st, s)) != hipSuccess) ||
+        ((g->t2 || g->tb2) && (e = launch_zero_field(L, g->uD, g->st, s)) != hipSuccess) ||
         (e = launch_zero_field(L, g->vel, Store::F32, s)) != hipSuccess ||
         (e = (g->pq ? launch_zero_field(L, g->pq, Store::F16, s) : launch_zero_field(L, g->p, Store::F32, s))) !=
             hipSuccess)
         return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
+    for (int i = 0; i < tb2_scratch(g->tb2); ++i)
+        if ((e = launch_zero_field(L, g->ws + wp.scr + wp.field_bytes * (size_t)i, g->st, s)) != hipSuccess)
+            return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
     const int phys[3] = {desc->shape[0], desc->ndim == 3 ? desc->shape[1] : 1,
                          desc->ndim == 3 ? desc->shape[2] : desc->shape[1]};
     if ((e = launch_fill_velocity(L, vp_dev, desc->vp_padded, desc->nbl, phys, g->vel, s)) != hipSuccess ||
@@ -1014,7 +1138,7 @@ extern "C" int fd_grid_get_info(const fd_grid *g, fd_grid_info *info) {
     info->tile[1] = g->d.ndim == 3 ? tile3_y(tw4) : kTile2Z;
     info->tile_strip = g->nstrip > 0 ? g->L.nx - 64 * g->ntx : 0;
     info->zchunk = g->zchunk[kPlain];
-    info->time_block = g->t2 ? 2 : 1;
+    info->time_block = g->t2 ? 2 : std::max(1, g->tb2);
     info->param_storage = g->d.param_storage;
     info->param_base = g->pq && g->dt_cached > 0.0 ? g->pq_base : 0.0;
     info->param_step = g->pq && g->dt_cached > 0.0 ? g->pq_step : 0.0;
@@ -1040,6 +1164,27 @@ int fdi_forward_steps(fd_grid *g, const fd_shot *sh, int nt, int n0, int n1, flo
     auto row = [&](int r) -> float * {
         return (rec_out && r >= 0 && r < nt && r >= g->rows_done) ? rec_out + (size_t)r * sh->nrec : nullptr;
     };
+    if (g->tb2) {
+        // 2D, several levels per launch; every row up to n1 is written here
+        void *fields[4] = {g->uA, g->uB, g->uC, g->uD};
+        Tb2Run run(g, kPlain, fields, g->cur, g->prev, 0, inj_scale, 1, sh->nrec, smp_scale, s);
+        for (int n = n0; n < n1;) {
+            if (ckpt && n % K == 0) {
+                HIPCHK(hipMemcpyAsync(ckpt[2 * (n / K)], run.cur, g->wp.field_bytes, hipMemcpyDeviceToDevice, s));
+                HIPCHK(hipMemcpyAsync(ckpt[2 * (n / K) + 1], run.prev, g->wp.field_bytes, hipMemcpyDeviceToDevice, s));
+            }
+            int lev = std::min(g->tb2, n1 - n);
+            if (ckpt) lev = std::min(lev, K - n % K);
+            int rc = run.advance(lev, sh->src_wavelet ? sh->src_wavelet + (size_t)n * sh->nsrc : nullptr, sh->nsrc,
+                                 rec_out ? rec_out + (size_t)n * sh->nrec : nullptr, sh->nrec, nullptr, nullptr);
+            if (rc) return rc;
+            n += lev;
+        }
+        g->cur = run.cur;
+        g->prev = run.prev;
+        g->rows_done = n1;
+        return run.flush();
+    }
     const bool t2 = g->t2 && !ckpt;
     int n = n0;
     while (n < n1) {
@@ -1199,6 +1344,19 @@ extern "C" int fd_adjoint(fd_grid *g, const fd_shot *sh, int nt, double dt,
                                                : std::exp2(std::round(std::log2((double)g->amp * dt * dt / g->cell)));
     const float inj_scale = (float)(amp_adj / (dt * dt));
     const float smp_scale = (float)(dt * dt / (g->cell * amp_adj));
+    if (g->tb2) {
+        void *fields[4] = {g->uA, g->uB, g->uC, g->uD};
+        Tb2Run run(g, kPlain, fields, A, B, 1, inj_scale, 0, sh->nsrc, smp_scale, s);
+        for (int k = nt; k >= 1;) {   // step k gives lambda^{k-1}, row k-1 of the output
+            const int lev = std::min(g->tb2, k);
+            if ((rc = run.advance(lev, residual ? residual + (size_t)(k - 1) * sh->nrec : nullptr, -(long long)sh->nrec,
+                                  src_adj ? src_adj + (size_t)(k - 1) * sh->nsrc : nullptr, -(long long)sh->nsrc,
+                                  nullptr, nullptr)))
+                return rc;
+            k -= lev;
+        }
+        return run.flush();
+    }
     for (int k = nt; k >= 1; --k) {
         a.u = A;
         a.prev = B;
@@ -1245,7 +1403,10 @@ GradPlan grad_plan(const fd_grid *g, int nt, int nrec, int K, int flags) {
     // two working fields for the resident and binomial schedules (the fixed
     // interval recomputes each segment in its checkpoint's fields)
     p.rot = o;
-    if (p.binomial || K >= nt) o += fb * 2;
+    // (with several levels per launch a segment's recompute rotates through
+    // its checkpoint's fields and these two, the resident schedule's forward
+    // pass through the grid's four)
+    if (p.binomial || (g->tb2 ? K < nt : K >= nt)) o += fb * 2;
     p.br = o; o += fb * (size_t)p.nbr;
     p.grad = o; o = align_up(o + sizeof(double) * (size_t)g->L.elems, 256);
     p.gpart = o; o = align_up(o + sizeof(float) * (size_t)g->L.elems, 256);
@@ -1298,7 +1459,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     const size_t fb = g->wp.field_bytes;
     std::vector<void *> ck((size_t)2 * gp.ncp);
     for (int i = 0; i < 2 * gp.ncp; ++i) ck[i] = ws + gp.ckpt + fb * (size_t)i;
-    void *rotA = ws + gp.rot, *rotB = ws + gp.rot + fb;   // (not allocated for the fixed interval, which does not use them)
+    void *rotA = ws + gp.rot, *rotB = ws + gp.rot + fb;   // (allocated for the schedules that use them, see grad_plan)
     std::vector<float *> br(gp.nbr);
     for (int i = 0; i < gp.nbr; ++i) br[i] = (float *)(ws + gp.br + fb * (size_t)i);
     double *gacc = (double *)(ws + gp.grad);
@@ -1357,7 +1518,57 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     HIPCHK(launch_zero_f64(gacc, L.elems, s));
     HIPCHK(launch_zero_field(L, gpart, Store::F32, s));
 
-    if (!gp.binomial && K >= nt) {
+    if (g->tb2 && !gp.binomial) {
+        // 2D, several levels per launch: the fixed-interval schedule below
+        // (the resident one is its case of a single segment)
+        const int clast = (gp.nseg - 1) * K;
+        void *fields[4] = {g->uA, g->uB, g->uC, g->uD};
+        // bracket steps n0 .. n1-1 into br[0 ..], the rows sampled into recb when rec is set
+        auto brackets = [&](Tb2Run &run, int n0, int n1, bool rec) -> int {
+            for (int n = n0; n < n1;) {
+                const int lev = std::min(g->tb2, n1 - n);
+                const int rc2 = run.advance(lev, sh->src_wavelet + (size_t)n * sh->nsrc, sh->nsrc,
+                                            rec ? recb + (size_t)n * sh->nrec : nullptr, sh->nrec, &br[n - n0], nullptr);
+                if (rc2) return rc2;
+                n += lev;
+            }
+            return run.flush();
+        };
+        if ((rc = fdi_forward_zero_state(g, s))) return rc;
+        if (clast > 0 && (rc = fdi_forward_steps(g, sh, nt, 0, clast, recb, ck.data(), K, s))) return rc;
+        Tb2Run last(g, kBracket, fields, g->cur, g->prev, 0, fwd_inj, 1, sh->nrec, 1.f, s);
+        if ((rc = brackets(last, clast, nt, true))) return rc;
+        HIPCHK(launch_misfit(recb, d_obs, nres, given, resid, g->partials, kNPart, misfit, s));
+        HIPCHK(launch_zero_field(L, g->uA, g->st, s));
+        HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+        if (clast > 0) {   // (their halo and pad cells are read as zero)
+            HIPCHK(launch_zero_field(L, rotA, g->st, s));
+            HIPCHK(launch_zero_field(L, rotB, g->st, s));
+        }
+        Tb2Run adj(g, kImage, fields, g->uA, g->uB, 1, adj_inj, 0, sh->nsrc, adj_smp, s);
+        for (int seg = gp.nseg - 1; seg >= 0; --seg) {
+            const int c = seg * K, e = std::min(c + K, nt);
+            if (c != clast) {
+                void *cf[4] = {ck[2 * seg], ck[2 * seg + 1], rotA, rotB};
+                Tb2Run rec(g, kBracket, cf, cf[0], cf[1], 0, fwd_inj, 1, 0, 1.f, s);
+                if ((rc = brackets(rec, c, e, false))) return rc;
+            }
+            for (int k = e; k >= c + 1;) {
+                // (a launch does not cross a fold of the partial gradient)
+                const int lev = std::min(std::min(g->tb2, k - c), kFoldEvery - adj_done % kFoldEvery);
+                float *rbr[kTb2MaxLev];
+                for (int t = 0; t < lev; ++t) rbr[t] = br[k - 1 - t - c];
+                if ((rc = adj.advance(lev, resid + (size_t)(k - 1) * sh->nrec, -(long long)sh->nrec,
+                                      src_adj ? src_adj + (size_t)(k - 1) * sh->nsrc : nullptr, -(long long)sh->nsrc,
+                                      rbr, gpart)))
+                    return rc;
+                k -= lev;
+                adj_done += lev;
+                if (adj_done % kFoldEvery == 0) HIPCHK(launch_fold_f64(L, gacc, gpart, s));
+            }
+        }
+        if ((rc = adj.flush())) return rc;
+    } else if (!gp.binomial && K >= nt) {
         // Every bracket fits the workspace: the forward pass itself writes
         // the bracket of each level (no checkpoint, no recompute), then the
         // residual, then the whole adjoint sweep.
@@ -1516,7 +1727,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     }
     if (adj_done % kFoldEvery) HIPCHK(launch_fold_f64(L, gacc, gpart, s));
     HIPCHK(launch_field_to_dense_f64(L, gacc, (flags & FD_GRAD_VELOCITY) ? g->vel : nullptr, grad_m, s));
-    if (src_adj) {
+    if (src_adj && !(g->tb2 && !gp.binomial)) {
         Sample sm = make_sample(g, 0, sh->nsrc, src_adj, adj_smp);
         HIPCHK(launch_sample(sm, LA, g->st, s));
     }

@@ -144,6 +144,61 @@ struct StepArgs {
 
 enum class Store { F32 = 0, F16 = 1, BF16 = 2 };
 
+// 2D step of several levels per launch (k_step2d_tb).
+constexpr int kTb2MaxLev = 8;    // levels per launch at most
+constexpr int kTb2Halo = 16;     // radius x levels at most
+
+// Samples of several levels (fields of one layout) at the same points: row i
+// of the output, at out + i * ostride, from field[i].
+struct SampleRows {
+    int npts, nc, lpp;            // as in Sample
+    int nrows;
+    int bpr;                      // workgroups per row
+    const long long *idx;
+    const float *w;
+    const void *field[kTb2MaxLev];
+    float *out;
+    long long ostride;
+    float scale;
+};
+
+// Levels n+1 .. n+nlev from u^n and u^{n-1}.  out and outp (unless nlev is
+// 1) receive the last two; they are none of the fields read.
+struct Step2Args {
+    Layout L;
+    const void *u, *prev;
+    void *out, *outp;
+    const float *p, *damp;
+    float w0, wx[kMaxR + 1], wz[kMaxR + 1];
+    int nlev;
+    int ntx;                      // tiles along x (set by the launcher)
+    // injection: as in Inject, with corner = (x, z, beg, end); level t takes
+    // the row vals + t * vstride (vals null: none)
+    const int *inj_pp;
+    const int4 *corner;
+    const int *src;
+    const float *w;
+    const float *vals;
+    long long vstride;
+    float scale;
+    int one_entry;                // every injected point has one entry, of its own index
+    // sampling: tiles with points of node_pp (per-column plane pointers; null:
+    // none) store level t + 1 < n + nlev - 1 in lev_out[t]; smp are the rows of
+    // the launch before, sampled by nsamp_blocks trailing workgroups
+    const int *node_pp;
+    void *lev_out[kTb2MaxLev];
+    SampleRows smp;
+    int nsamp_blocks;
+    // gradient modes: the bracket of level t, and the partial gradient
+    float *br_out[kTb2MaxLev];
+    const float *br_in[kTb2MaxLev];
+    float *gpart;
+};
+int step2d_levels(const Layout &L);   // levels per launch of a 2D grid, 0: k_step2d
+int sample_rows_blocks(int npts, int lpp);   // workgroups per row of launch_sample_rows
+hipError_t launch_step2d_tb(Step2Args a, Store st, int mode, hipStream_t s);
+hipError_t launch_sample_rows(const SampleRows &smp, Store st, hipStream_t s);
+
 // Resident workgroups per CU of a step kernel (0 if unknown).
 int step_blocks_per_cu(int ndim, int r, Store st, int mode, int shape3, bool pq);
 

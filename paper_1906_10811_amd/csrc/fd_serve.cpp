@@ -95,10 +95,18 @@ struct Footprint {
     size_t grid, vp, wav, rec, total;
 };
 
+// 2D shots run one step per launch here: several levels per launch would
+// reserve more fields per shot, and the budget is what admits them.
+void serve_desc(fd_grid_desc *d) {
+    if (d->ndim == 2) d->time_block = 1;
+}
+
 Footprint footprint(const fd_request *r) {
     Footprint f{};
     size_t gb = 0;
-    if (fd_grid_workspace_bytes(&r->grid, &gb) != FD_OK) return f;
+    fd_grid_desc d = r->grid;
+    serve_desc(&d);
+    if (fd_grid_workspace_bytes(&d, &gb) != FD_OK) return f;
     long long phys = 1;
     for (int a = 0; a < r->grid.ndim; ++a) phys *= r->grid.shape[a];
     f.grid = align_up(gb, 256);
@@ -478,6 +486,7 @@ extern "C" int fd_submit(fd_server *srv, const fd_request *req, uint64_t *ticket
             return fdi_fail(FD_ERR_ARG, "incomplete request");
         Req *r = new Req();
         r->desc = req->grid;
+        serve_desc(&r->desc);
         const int ndim = req->grid.ndim;
         long long phys = 1;
         for (int a = 0; a < ndim; ++a) phys *= req->grid.shape[a];

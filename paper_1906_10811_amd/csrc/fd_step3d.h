@@ -70,6 +70,7 @@ template <> struct Elem<Store::F32> {
     __device__ static Raw ld4raw(const T *p) { return ld4(p); }
     __device__ static Raw ld4ntraw(const T *p) { return ld4nt(p); }
     __device__ static float4 cvt(const Raw &r) { return r; }
+    __device__ static Raw raw(const float4 &v) { return v; }
     __device__ static void st4nt(T *p, float4 v) { st4nt_f32(p, v); }
     __device__ static void st4(T *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
     __device__ static float ld(const T *p) { return *p; }
@@ -102,6 +103,7 @@ template <typename Cvt> struct Elem16 {
     __device__ static Raw ld4raw(const T *p) { return *reinterpret_cast<const uint2 *>(p); }
     __device__ static Raw ld4ntraw(const T *p) { return ld2nt_u32(p); }
     __device__ static float4 cvt(const Raw &r) { return unpack(r); }
+    __device__ static Raw raw(const float4 &v) { return pack(v); }
     __device__ static void st4nt(T *p, float4 v) { st2nt_u32(p, pack(v)); }
     __device__ static void st4(T *p, float4 v) { *reinterpret_cast<uint2 *>(p) = pack(v); }
     __device__ static float ld(const T *p) { return Cvt::to_f(*p); }
@@ -153,13 +155,13 @@ __device__ inline int xcd_remap(int h, int G) {
     return (xcd < rem) ? xcd * (per + 1) + k : rem * (per + 1) + (xcd - rem) * per + k;
 }
 
-template <Store S>
+template <Store S, int NT = kBlock>   // NT lanes in the workgroup
 __device__ void sample_block(const Sample &s, const void *field, int blk) {
     using E = Elem<S>;
     // s.lpp lanes share a point: each sums a strided share of its nodes, then
     // the group reduces with xor shuffles (fixed order: deterministic).
     const int lane = (int)threadIdx.x;
-    const int i = blk * (kBlock / s.lpp) + lane / s.lpp;
+    const int i = blk * (NT / s.lpp) + lane / s.lpp;
     const int sub = lane & (s.lpp - 1);
     const typename E::T *f = (const typename E::T *)field;
     float v = 0.f;
@@ -214,9 +216,11 @@ __device__ inline void gather_sources(const Inject &inj, int e0, int e1, int x, 
 // no beta, and c - m is exact where the two levels are close.  The hardware
 // reciprocal of 1 is exactly 1 (checked, as for every power of two), so
 // outside the damping layer alpha is 1 with no select.
+__device__ inline float update_alpha(float c, float m, float p, float q, float alpha) {
+    return __builtin_fmaf(alpha, __builtin_fmaf(p, q, 2.f * (c - m)), m);
+}
 __device__ inline float update_point(float c, float m, float p, float lap, float src, float s) {
-    const float alpha = __builtin_amdgcn_rcpf(1.f + s);
-    return __builtin_fmaf(alpha, __builtin_fmaf(p, lap + src, 2.f * (c - m)), m);
+    return update_alpha(c, m, p, lap + src, __builtin_amdgcn_rcpf(1.f + s));
 }
 
 // The same update for the difference storage: with u^{n-1} = u^n - d,
@@ -254,6 +258,11 @@ __device__ inline void image_accumulate(float *g, int nvalid, const float un[4],
     }
 }
 
+// The imaging bracket of a level from its three levels, s = sigma dt / 2.
+__device__ inline float bracket_point(float u1, float u0, float um, float s) {
+    return __builtin_fmaf(s, u1 - um, (u1 - 2.f * u0) + um);
+}
+
 // Gradient epilogues of a step (float32 fields, pitched offset `off` of the
 // first of 4 points, nvalid of them inside the grid).
 template <int MODE>
@@ -263,8 +272,7 @@ __device__ inline void grad_epilogue(const Imaging &img, long long off, int nval
         float b[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float u1 = un[i], u0 = comp(c, i), um = comp(m, i);
-            b[i] = __builtin_fmaf(s[i], u1 - um, (u1 - 2.f * u0) + um);
+            b[i] = bracket_point(un[i], comp(c, i), comp(m, i), s[i]);
         }
         if (nvalid >= 4) {
             st4nt_f32(img.br_out + off, make_float4(b[0], b[1], b[2], b[3]));
