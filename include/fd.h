@@ -424,10 +424,11 @@ typedef struct fd_diffusion_desc {
     double spacing[2];     /* h_x, h_y > 0 */
     int space_order;       /* even, 2..16 */
     double nu;             /* diffusivity > 0 */
-    int time_block;        /* steps per launch: 0 = automatic (8 at so 2 and 4,
-                              4 at so 8, where the LDS-blocked kernel beats one
-                              step per launch, else 1), 1 = one step per launch,
-                              k > 1 = at most min(k, 16 / (so/2)) */
+    int time_block;        /* steps per launch: 0 = automatic (up to 8, by space
+                              order and grid size), 1 = one step per launch,
+                              k > 1 = the automatic choice, at most
+                              min(k, 16 / (so/2)); the result does not depend
+                              on it, bit for bit */
 } fd_diffusion_desc;
 
 /* Device workspace for fd_diffusion_run (two pitched float32 fields). */

@@ -22,7 +22,8 @@ ARCH = "gfx950"
 
 # the 3D step's instantiations are spread over units of similar size that
 # compile in parallel
-HIP_SOURCES = ["fd_kernels.hip", "fd_step2d.hip", "fd_step3d_f32.hip", "fd_step3d_f16.hip", "fd_step3d_f16_diff.hip",
+HIP_SOURCES = ["fd_kernels.hip", "fd_step2d.hip", "fd_diffuse2d.hip",
+               "fd_step3d_f32.hip", "fd_step3d_f16.hip", "fd_step3d_f16_diff.hip",
                "fd_step3d_bf16.hip", "fd_step3d_bf16_diff.hip"]
 HOST_SOURCES = ["fd_api.cpp", "fd_serve.cpp", "fd_diffusion.cpp", "fd_checkpoint.cpp"]
 

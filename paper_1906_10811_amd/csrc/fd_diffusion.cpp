@@ -94,23 +94,14 @@ int run_diffusion(const fd_diffusion_desc *desc, void *workspace, size_t ws_byte
         (e = launch_zero_field(L, B, Store::F32, s)) != hipSuccess ||
         (e = launch_dense_to_field(L, u0, A, Store::F32, 1.f, s)) != hipSuccess)
         return fdi_fail(FD_ERR_DEVICE, "diffusion setup: %s", hipGetErrorString(e));
-    // temporal blocking: each launch advances up to `per` levels from a tile
-    // staged with an r*per halo (the thesis's OPS tiling / YASK wave-front
-    // tiling idea, Section 2.2 and 2.3.1, in LDS)
-    // Automatic choice (measured on 2500^2 and 10000^2 for every radius and
-    // level count): 8 levels at radius 1 and 2, 4 at radius 4; at the other
-    // radii the redundant halo levels cost more than the HBM traffic they
-    // save, and one step per launch is faster.
-    int per = diffuse2d_max_levels(L.r);
-    if (desc->time_block > 0) per = std::min(per, desc->time_block);
-    else per = (L.r == 1 || L.r == 2) ? 8 : L.r == 4 ? 4 : 1;
+    // temporal blocking: each launch advances several levels (the thesis's OPS
+    // tiling / YASK wave-front tiling idea, Section 2.2 and 2.3.1, inside a
+    // wave or a workgroup)
     for (int n = 0; n < nt;) {
-        const int lev = std::min(per, nt - n);
-        if (per <= 1)
-            e = launch_diffuse2d(L, A, B, w0, wx, wz, s);
-        else
-            e = launch_diffuse2d_tb(L, A, B, w0, wx, wz, lev, s);
-        if (e != hipSuccess) return fdi_fail(FD_ERR_DEVICE, "diffusion step: %s", hipGetErrorString(e));
+        int lev = nt - n;
+        if (desc->time_block > 0) lev = std::min(lev, desc->time_block);
+        if ((e = launch_diffuse2d(L, A, B, w0, wx, wz, lev, &lev, s)) != hipSuccess)
+            return fdi_fail(FD_ERR_DEVICE, "diffusion step: %s", hipGetErrorString(e));
         std::swap(A, B);
         n += lev;
     }

@@ -234,14 +234,12 @@ hipError_t launch_dense_diff_to_field(const Layout &L, const float *a, const flo
                                       float scale, hipStream_t s);
 hipError_t launch_field_diff_to_dense(const Layout &L, const void *u, const void *d, float *dense, Store st,
                                       float scale, hipStream_t s);
-// One explicit diffusion step, 2D: out = u + w0 u + sum_j wx_j (..) + wz_j (..)
-// (weights already multiplied by nu dt).
+// Up to `most` explicit diffusion steps, 2D, in one launch, *levels of them:
+// u' = u + w0 u + sum_j wx_j (..) + wz_j (..) (weights already multiplied by
+// nu dt).  radius x levels is at most kDiffHalo.
+constexpr int kDiffHalo = 16;
 hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w0, const float *wx,
-                            const float *wz, hipStream_t s);
-// Temporally blocked variant: nlev (1 .. diffuse2d_max_levels(r)) steps per launch.
-int diffuse2d_max_levels(int r);
-hipError_t launch_diffuse2d_tb(const Layout &L, const float *u, float *out, float w0, const float *wx,
-                               const float *wz, int nlev, hipStream_t s);
+                            const float *wz, int most, int *levels, hipStream_t s);
 // Address of the static scratch (kStaticScratchBytes) on `device`, which
 // must be the current device; resolved with hipGetSymbolAddress on the
 // first call per device and kept.

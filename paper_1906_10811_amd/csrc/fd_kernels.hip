@@ -520,243 +520,6 @@ __global__ __launch_bounds__(kBlock) void k_step2d(const StepArgs a) {
     }
 }
 
-// ------------------------------------------------------- 2D diffusion step
-// The thesis's benchmark operator: one forward-Euler step of u_t = nu Lap u.
-// Tile 64 x 64 staged in LDS with an r halo; each lane updates 4 x points in
-// each of 4 rows.  Weights carry nu dt (hoisted on the host, no division).
-struct DiffArgs {
-    Layout L;
-    const float *u;
-    float *out;
-    float w0;
-    float wx[kMaxR + 1];
-    float wz[kMaxR + 1];
-    int ntx, ntz;
-    int out_cached;   // ordinary stores of the new level (small fields), else non-temporal
-};
-
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_diffuse2d(const DiffArgs a) {
-    constexpr int HX4 = (R + 3) / 4;
-    constexpr int W4 = 16 + 2 * HX4;
-    constexpr int LH = kTile2Z + 2 * R;
-    __shared__ float4 lds[LH * W4];
-    const Layout L = a.L;
-    const int t = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    const int bx = t % a.ntx, bz = t / a.ntx;
-    const int x0 = bx * kTileX, z0 = bz * kTile2Z;
-    const int lane = (int)threadIdx.x;
-    const long long zcol = L.offset((L.nx + 3) & ~3, 0, 0);
-    for (int i = lane; i < LH * W4; i += kBlock) {
-        const int lr = i / W4, c = i - lr * W4;
-        const int gz = z0 - R + lr, gx = x0 - 4 * HX4 + 4 * c;
-        const bool ok = gz >= 0 && gz < L.nz && gx >= 0 && gx < L.nx;
-        lds[i] = *reinterpret_cast<const float4 *>(a.u + (ok ? L.offset(gx, 0, gz) : zcol));
-    }
-    __syncthreads();
-    const int tx = lane & 15, tz = lane >> 4;
-    const int x = x0 + 4 * tx;
-    if (x >= L.nx) return;
-    const int nvalid = L.nx - x;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int z = z0 + tz * 4 + rr;
-        if (z >= L.nz) break;
-        const float4 *row = lds + (R + tz * 4 + rr) * W4 + HX4 + tx;
-        float xs[4 * (2 * HX4 + 1)];
-#pragma unroll
-        for (int c = -HX4; c <= HX4; ++c) {
-            const float4 v = row[c];
-            xs[4 * (c + HX4) + 0] = v.x;
-            xs[4 * (c + HX4) + 1] = v.y;
-            xs[4 * (c + HX4) + 2] = v.z;
-            xs[4 * (c + HX4) + 3] = v.w;
-        }
-        float un[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) un[i] = a.w0 * xs[4 * HX4 + i];
-#pragma unroll
-        for (int j = 1; j <= R; ++j) {
-            const float4 zp = row[j * W4], zm = row[-j * W4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float acc = a.wx[j] * (xs[4 * HX4 + i + j] + xs[4 * HX4 + i - j]);
-                acc += a.wz[j] * (comp(zp, i) + comp(zm, i));
-                un[i] += acc;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) un[i] += xs[4 * HX4 + i];
-        const long long off = L.offset(x, 0, z);
-        if (nvalid >= 4) {
-            const float4 r4 = make_float4(un[0], un[1], un[2], un[3]);
-            if (a.out_cached)
-                *reinterpret_cast<float4 *>(a.out + off) = r4;
-            else
-                st4nt_f32(a.out + off, r4);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                if (i < nvalid) a.out[off + i] = un[i];
-        }
-    }
-}
-
-// Temporally blocked diffusion: one launch advances `nlev` (<= 16/R) levels.
-// A workgroup stages its 64 x 64 output tile plus an H = R*nlev halo in z and
-// an H rounded up to a multiple of 4 in x (zero outside the grid; the
-// rounding keeps every staged row and the written tile on 16-byte
-// boundaries at odd H) in one LDS buffer and updates it in place level by
-// level on the shrinking region that stays exact: level t is computed on
-// rows and 4-point groups at least R*t from the staged border (rounded out
-// to whole groups; the rounding margin holds values that nothing exact
-// reads).  Between levels each lane keeps its new values in registers
-// across a barrier, so one buffer suffices.  HBM traffic: 8 B per point per
-// launch, i.e. 8/nlev B per point and step.
-constexpr int kTbHalo = 16;                        // R * levels per launch, at most
-constexpr int kTbRows = kTile2Z + 2 * kTbHalo;     // 96 staged rows
-constexpr int kTbPadX = 4;                         // zero floats left/right of a staged row
-constexpr int kTbW4 = (kTileX + 2 * kTbHalo + 2 * kTbPadX) / 4;   // float4 per staged row
-constexpr int kTbPerLane = (kTbRows * kTbW4 + kBlock - 1) / kBlock;   // staged float4 groups per lane
-
-// The LDS buffer (40 KB) allows four workgroups, i.e. four waves per SIMD.
-// At radii 3, 5 and 7 the compiler's own allocation (137-154 VGPRs) allows
-// only three, so those radii are held to four waves per SIMD (97-101 VGPRs,
-// no spills: 5-15 % faster); at the other radii the default allocation
-// already fits four waves, and the same bound made radius 2 slower.
-
-template <int R>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu((R & 1) && R > 1 ? 4 : 1))) void k_diffuse2d_tb(const DiffArgs a, int nlev) {
-    __shared__ float4 lds[kTbRows * kTbW4];
-    const Layout L = a.L;
-    const int t0 = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    const int bx = t0 % a.ntx, bz = t0 / a.ntx;
-    const int H = R * nlev;                       // staged halo of this launch in z
-    const int Hx = (H + 3) & ~3;                  // and in x, whole float4 groups
-    const int x0 = bx * kTileX - Hx, z0 = bz * kTile2Z - H;   // grid coords of staged (0, 0)
-    const int rows = kTile2Z + 2 * H;
-    const int g4 = kTbW4;                         // staged float4 per row: the full LDS row, so every
-                                                  // neighbour group a level reads holds grid data or zero
-    const int lane = (int)threadIdx.x;
-    // stage level 0; float4 column c covers grid x = x0 - 4 + 4c (a float4
-    // load when that is 16-B aligned in the grid, else element by element)
-    for (int i = lane; i < rows * g4; i += kBlock) {
-        const int lr = i / g4, c = i - lr * g4;
-        const int gz = z0 + lr, gx = x0 - kTbPadX + 4 * c;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gz >= 0 && gz < L.nz && gx + 3 >= 0 && gx < L.nx) {
-            if (gx >= 0 && (gx & 3) == 0) {
-                v = *reinterpret_cast<const float4 *>(a.u + L.offset(gx, 0, gz));
-            } else {
-                float e[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int xx = gx + k;
-                    e[k] = (xx >= 0 && xx < L.nx) ? a.u[L.offset(xx, 0, gz)] : 0.f;
-                }
-                v = make_float4(e[0], e[1], e[2], e[3]);
-            }
-        }
-        lds[lr * kTbW4 + c] = v;
-    }
-    __syncthreads();
-    const float *ldsf = reinterpret_cast<const float *>(lds);
-    // Each lane owns fixed float4 groups of the staged tile (row-major with
-    // the constant row stride, so the index split is a multiply-shift); a
-    // level updates the groups inside its exact region.  Neighbours are read
-    // as whole float4 groups: x from the 2 ceil(R/4) + 1 groups of the row,
-    // z from the groups j rows up and down (conflict-free 16-byte LDS reads).
-    constexpr int HX4 = (R + 3) / 4;
-    for (int t = 1; t <= nlev; ++t) {
-        // level t region: rows [R t, rows - R t), float4 columns [c0, c1)
-        const int r0 = R * t, r1 = rows - R * t;
-        const int c0 = 1 + (R * t) / 4;                        // first float4 column (pad column is 0)
-        const int c1 = 1 + (kTileX + 2 * Hx - R * t + 3) / 4;  // one past the last
-        float4 res[kTbPerLane];
-#pragma unroll
-        for (int k = 0; k < kTbPerLane; ++k) {
-            const int gidx = lane + k * kBlock;
-            const int lr = gidx / kTbW4, c = gidx - lr * kTbW4;
-            res[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (lr >= r0 && lr < r1 && c >= c0 && c < c1) {
-                const float4 *row = lds + lr * kTbW4 + c;
-                float xs[4 * (2 * HX4 + 1)];
-#pragma unroll
-                for (int q = -HX4; q <= HX4; ++q) {
-                    const float4 v = row[q];
-                    xs[4 * (q + HX4) + 0] = v.x;
-                    xs[4 * (q + HX4) + 1] = v.y;
-                    xs[4 * (q + HX4) + 2] = v.z;
-                    xs[4 * (q + HX4) + 3] = v.w;
-                }
-                float un[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) un[i] = a.w0 * xs[4 * HX4 + i];
-#pragma unroll
-                for (int j = 1; j <= R; ++j) {
-                    const float4 zp = row[j * kTbW4], zm = row[-j * kTbW4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float acc = a.wx[j] * (xs[4 * HX4 + i + j] + xs[4 * HX4 + i - j]);
-                        acc += a.wz[j] * (comp(zp, i) + comp(zm, i));
-                        un[i] += acc;
-                    }
-                }
-                const int gz = z0 + lr;
-                const int gx = x0 - kTbPadX + 4 * c;
-                float o[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bool in = gz >= 0 && gz < L.nz && gx + i >= 0 && gx + i < L.nx;
-                    o[i] = in ? un[i] + xs[4 * HX4 + i] : 0.f;   // the field is zero outside the grid
-                }
-                res[k] = make_float4(o[0], o[1], o[2], o[3]);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kTbPerLane; ++k) {
-            const int gidx = lane + k * kBlock;
-            const int lr = gidx / kTbW4, c = gidx - lr * kTbW4;
-            if (lr >= r0 && lr < r1 && c >= c0 && c < c1) lds[lr * kTbW4 + c] = res[k];
-        }
-        __syncthreads();
-    }
-    // write the 64 x 64 tile
-    for (int i = lane; i < kTile2Z * (kTileX / 4); i += kBlock) {
-        const int lr = i / (kTileX / 4), cq = i - lr * (kTileX / 4);
-        const int gz = z0 + H + lr, gx = x0 + Hx + 4 * cq;
-        if (gz >= L.nz || gx >= L.nx) continue;
-        const int c = (kTbPadX + Hx) / 4 + cq;         // float4 column of the written group
-        const float *src = ldsf + ((H + lr) * kTbW4 + c) * 4;
-        const int nvalid = L.nx - gx;
-        const long long off = L.offset(gx, 0, gz);
-        if (nvalid >= 4) {
-            const float4 r4 = lds[(H + lr) * kTbW4 + c];
-            if (a.out_cached)
-                *reinterpret_cast<float4 *>(a.out + off) = r4;
-            else
-                st4nt_f32(a.out + off, r4);
-        } else {
-            for (int k = 0; k < nvalid; ++k) a.out[off + k] = src[k];
-        }
-    }
-}
-
-template <int... Rs>
-struct DiffTable {
-    static void (*get(int r))(const DiffArgs) {
-        void (*f)(const DiffArgs) = nullptr;
-        ((r == Rs ? (f = k_diffuse2d<Rs>, 0) : 0), ...);
-        return f;
-    }
-    static void (*get_tb(int r))(const DiffArgs, int) {
-        void (*f)(const DiffArgs, int) = nullptr;
-        ((r == Rs ? (f = k_diffuse2d_tb<Rs>, 0) : 0), ...);
-        return f;
-    }
-};
-
 template <Store S>
 __global__ void k_sample(const Sample s, const void *field) {
     sample_block<S>(s, field, (int)blockIdx.x);
@@ -1247,48 +1010,6 @@ hipError_t launch_field_to_dense_f64(const Layout &L, const double *f, const flo
                                      hipStream_t s) {
     const long long n = (long long)L.nx * L.ny * L.nz;
     hipLaunchKernelGGL(k_field_to_dense_f64, dim3(grid_for(n)), dim3(kBlock), 0, s, L, f, vel, dense);
-    return hipGetLastError();
-}
-
-hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w0, const float *wx,
-                            const float *wz, hipStream_t s) {
-    auto f = DiffTable<1, 2, 3, 4, 5, 6, 7, 8>::get(L.r);
-    if (!f || L.ndim != 2) return hipErrorInvalidValue;
-    DiffArgs a{};
-    a.L = L;
-    a.u = u;
-    a.out = out;
-    a.w0 = w0;
-    for (int j = 0; j <= kMaxR; ++j) {
-        a.wx[j] = wx[j];
-        a.wz[j] = wz[j];
-    }
-    a.ntx = (L.nx + kTileX - 1) / kTileX;
-    a.ntz = (L.nz + kTile2Z - 1) / kTile2Z;
-    a.out_cached = (size_t)L.elems * sizeof(float) <= kCachedField;
-    hipLaunchKernelGGL(f, dim3(a.ntx * a.ntz), dim3(kBlock), 0, s, a);
-    return hipGetLastError();
-}
-
-int diffuse2d_max_levels(int r) { return kTbHalo / r; }
-
-hipError_t launch_diffuse2d_tb(const Layout &L, const float *u, float *out, float w0, const float *wx,
-                               const float *wz, int nlev, hipStream_t s) {
-    auto f = DiffTable<1, 2, 3, 4, 5, 6, 7, 8>::get_tb(L.r);
-    if (!f || L.ndim != 2 || nlev < 1 || L.r * nlev > kTbHalo) return hipErrorInvalidValue;
-    DiffArgs a{};
-    a.L = L;
-    a.u = u;
-    a.out = out;
-    a.w0 = w0;
-    for (int j = 0; j <= kMaxR; ++j) {
-        a.wx[j] = wx[j];
-        a.wz[j] = wz[j];
-    }
-    a.ntx = (L.nx + kTileX - 1) / kTileX;
-    a.ntz = (L.nz + kTile2Z - 1) / kTile2Z;
-    a.out_cached = (size_t)L.elems * sizeof(float) <= kCachedField;
-    hipLaunchKernelGGL(f, dim3(a.ntx * a.ntz), dim3(kBlock), 0, s, a, nlev);
     return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace fd {
 
@@ -42,6 +43,7 @@ namespace {
 // planes are re-read as halo by the neighbouring tiles.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float4 ld4nt_f32(const float *p) {
     const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
@@ -294,6 +296,38 @@ __device__ __forceinline__ void static_for(F &&f) {
         f(std::integral_constant<int, B>{});
         static_for<B + 1, E>(f);
     }
+}
+
+// f(integral_constant<I>) && ... in order, stopping at the first false.
+template <int... Is, typename F>
+__device__ __forceinline__ bool all_of_seq(std::integer_sequence<int, Is...>, F &&f) {
+    return (f(std::integral_constant<int, Is>{}) && ...);
+}
+
+// Buffer accesses of 4 consecutive points at a uniform address plus a 32-bit
+// lane offset in bytes.  Offsets from kOob on are outside the buffer's range:
+// loads return zero, stores are dropped.  AUX: kNt for the non-temporal hint,
+// else 0.
+constexpr int kNt = 2;
+constexpr int kBufBytes = 0x7FFFFFFF;
+constexpr int kOob = (int)0x80000000;
+
+__device__ inline __amdgpu_buffer_rsrc_t buf_rsrc(const void *p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, kBufBytes, 0x00027000);
+}
+template <Store S, int AUX>
+__device__ inline typename Elem<S>::Raw bufld4(const typename Elem<S>::T *p, int off) {
+    if constexpr (S == Store::F32)
+        return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(buf_rsrc(p), off, 0, AUX));
+    else
+        return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(buf_rsrc(p), off, 0, AUX));
+}
+template <Store S, int AUX>
+__device__ inline void bufst4(typename Elem<S>::T *p, int off, const typename Elem<S>::Raw &v) {
+    if constexpr (S == Store::F32)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buf_rsrc(p), off, 0, AUX);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), buf_rsrc(p), off, 0, AUX);
 }
 
 // Shared memory of a 3D step workgroup with tiles of TW float4 columns,
