@@ -96,17 +96,23 @@ inline int sample_blocks(const Sample &s) {
 // from the three levels it holds in registers; an adjoint step (kImage)
 // then accumulates grad -= lam^n * br^n for its new value lam^n into a
 // float32 partial sum, which the host folds into the float64 gradient every
-// few steps.  br and the partial sum use the pitched field layout.
+// few steps.  br and the partial sum use the pitched field layout.  kImage3
+// accumulates for the three levels the step holds, lam^{n+2} (its previous
+// field), lam^{n+1} (its centre) and lam^n, in that order: the two steps
+// before it are then plain ones, and three steps read and write the partial
+// sum once.
 struct Imaging {
     float *br_out;          // kBracket: bracket of the step's time level
-    const float *br_in;     // kImage: bracket of the step's time level
+    const float *br_in[3];  // kImage: bracket of the step's time level; kImage3: of n+2, n+1, n
     float *gpart;           // kImage: float32 partial sum, folded into float64 by the host loop
 };
 
 // kDiff (16-bit 3D storage only): the grid keeps u^n and the difference
 // delta = u^n - u^{n-1}; `prev` is the difference field (read at the point),
 // `out` receives u^{n+1} and `out2` the new difference (in place of `prev`).
-enum StepMode { kPlain = 0, kBracket = 1, kImage = 2, kDiff = 3 };
+// (kImage3: 3D only)
+enum StepMode { kPlain = 0, kBracket = 1, kImage = 2, kDiff = 3, kImage3 = 4 };
+constexpr int kStepModes = 5;
 
 struct StepArgs {
     Layout L;

@@ -747,7 +747,7 @@ using Tab2 = Table2<S, MODE, 1, 2, 3, 4, 5, 6, 7, 8>;
 StepFn pick_step(int ndim, int r, Store st, int mode, int tw4, bool pq) {
     if (ndim == 3) {
         if (pq && mode != kPlain && mode != kDiff) return nullptr;
-        if ((mode == kBracket || mode == kImage) && st != Store::F32) return nullptr;
+        if ((mode == kBracket || mode == kImage || mode == kImage3) && st != Store::F32) return nullptr;
         if (mode == kDiff && st == Store::F32) return nullptr;
         switch (st) {
             case Store::F32: return step3d_kernel_f32(r, mode, tw4, pq);
@@ -757,7 +757,7 @@ StepFn pick_step(int ndim, int r, Store st, int mode, int tw4, bool pq) {
         }
         return nullptr;
     }
-    if (pq || mode == kDiff) return nullptr;
+    if (pq || mode == kDiff || mode == kImage3) return nullptr;
     if (mode == kBracket) return st == Store::F32 ? Tab2<Store::F32, kBracket>::get(r) : nullptr;
     if (mode == kImage) return st == Store::F32 ? Tab2<Store::F32, kImage>::get(r) : nullptr;
     switch (st) {

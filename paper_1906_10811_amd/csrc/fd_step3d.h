@@ -240,16 +240,13 @@ __device__ inline float lap_term2(float wx, float xs, float wz, float zs) {
     return __builtin_fmaf(wz, zs, wx * xs);
 }
 
-// g -= lam * br for the lane's 4 points into the float32 partial sum (the
-// host folds it into the float64 gradient every few adjoint steps); gv is
-// the partial sum's current value at those points.
-__device__ inline void image_accumulate(float *g, int nvalid, const float un[4], const float4 &br,
-                                        const float4 &gv) {
-    float4 v;
-    v.x = __builtin_fmaf(-un[0], br.x, gv.x);
-    v.y = __builtin_fmaf(-un[1], br.y, gv.y);
-    v.z = __builtin_fmaf(-un[2], br.z, gv.z);
-    v.w = __builtin_fmaf(-un[3], br.w, gv.w);
+// g - lam * br for the lane's 4 points, g the float32 partial sum (the host
+// folds it into the float64 gradient every few adjoint steps).
+__device__ inline float4 image_term(const float lam[4], const float4 &br, const float4 &g) {
+    return make_float4(__builtin_fmaf(-lam[0], br.x, g.x), __builtin_fmaf(-lam[1], br.y, g.y),
+                       __builtin_fmaf(-lam[2], br.z, g.z), __builtin_fmaf(-lam[3], br.w, g.w));
+}
+__device__ inline void image_accumulate(float *g, int nvalid, const float4 &v) {
     if (nvalid >= 4) {
         st4nt_f32(g, v);
     } else {
@@ -284,7 +281,8 @@ __device__ inline void grad_epilogue(const Imaging &img, long long off, int nval
                 if (i < nvalid) img.br_out[off + i] = b[i];
         }
     } else if constexpr (MODE == kImage) {
-        image_accumulate(img.gpart + off, nvalid, un, ld4nt_f32(img.br_in + off), ld4nt_f32(img.gpart + off));
+        image_accumulate(img.gpart + off, nvalid,
+                         image_term(un, ld4nt_f32(img.br_in[0] + off), ld4nt_f32(img.gpart + off)));
     }
 }
 
@@ -464,7 +462,7 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
     // from HBM and ran 1.7 % slower (the step is HBM-bound there); in the
     // imaging mode it needs registers that cost a workgroup per CU.
     constexpr int NQ = 2 * R + 1;
-    constexpr bool kRot = MODE != kImage && (R == 1 || R == 7 || (S != Store::F32 && R >= 5));
+    constexpr bool kRot = MODE != kImage && MODE != kImage3 && (R == 1 || R == 7 || (S != Store::F32 && R >= 5));
     constexpr int NQP = kRot ? (NQ + 2) / 3 * 3 : NQ;
     constexpr int UNR = kRot ? NQP : 3;
     float4 q[NQP];
@@ -491,11 +489,13 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
     // which would otherwise wait for the loads they move.  (A fourth set,
     // three planes ahead, measured 1-2.5 % slower.)
     using Raw = typename E::Raw;
+    constexpr bool kImaging = MODE == kImage || MODE == kImage3;
+    constexpr int NBR = MODE == kImage3 ? 3 : 1;
     struct PlaneRegs {
         Raw front, mv;
         std::conditional_t<PQ, uint2, float4> pv;   // p as stored
         Raw hv[HPT];      // halo of plane z+R
-        float4 br, gp;    // imaging step: bracket and partial gradient of plane z
+        float4 br[NBR], gp;   // imaging steps: brackets and partial gradient of plane z
     };
     auto issue = [&](PlaneRegs &r, int st) __attribute__((always_inline)) {
         st = min(st, len - 1);   // past the chunk: a harmless in-bounds reload
@@ -511,8 +511,9 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
         else
             r.pv = ld4nt_f32(Pp + base + zo);
         r.mv = E::ld4ntraw(Pv + base + zo);
-        if constexpr (MODE == kImage) {
-            r.br = ld4nt_f32(a.img.br_in + base + zo);
+        if constexpr (kImaging) {
+#pragma unroll
+            for (int k = 0; k < NBR; ++k) r.br[k] = ld4nt_f32(a.img.br_in[k] + base + zo);
             r.gp = ld4nt_f32(a.img.gpart + base + zo);
         }
     };
@@ -654,8 +655,14 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
 #pragma unroll
                 for (int i = 0; i < 4; ++i) sv[i] = sxy[i] + sz;
                 grad_epilogue<MODE>(a.img, off, nvalid, un, QQ(R), mvf, sv);
-            } else if constexpr (MODE == kImage) {
-                image_accumulate(a.img.gpart + off, nvalid, un, cur.br, cur.gp);
+            } else if constexpr (kImaging) {
+                float4 g = cur.gp;
+                if constexpr (MODE == kImage3) {
+                    const float l2[4] = {mvf.x, mvf.y, mvf.z, mvf.w};
+                    const float l1[4] = {QQ(R).x, QQ(R).y, QQ(R).z, QQ(R).w};
+                    g = image_term(l1, cur.br[1], image_term(l2, cur.br[0], g));
+                }
+                image_accumulate(a.img.gpart + off, nvalid, image_term(un, cur.br[NBR - 1], g));
             }
         }
         if constexpr (!kRot) {

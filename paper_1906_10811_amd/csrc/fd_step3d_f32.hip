@@ -12,6 +12,7 @@ StepFn step3d_kernel_f32(int r, int mode, int shape, bool pq) {
         case kPlain: return step3d_get<Store::F32, kPlain>(r, shape, pq);
         case kBracket: return step3d_get<Store::F32, kBracket>(r, shape, pq);
         case kImage: return step3d_get<Store::F32, kImage>(r, shape, pq);
+        case kImage3: return step3d_get<Store::F32, kImage3>(r, shape, pq);
     }
     return nullptr;
 }
