@@ -1014,7 +1014,7 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
             const int occ = std::max(1, step_blocks_per_cu(3, L.r, g->st, mk, g->shape3, g->pq != nullptr));
             const int tiles = std::max(1, g->ntx * g->nty + g->nstrip);
             const int kmax = std::min(occ, 3), prefer = g->st == Store::F32 ? 2 : 3;
-            int nzc = 1;
+            int nzc = 1, kbest = std::min(2, kmax);
             double best = -1.0;
             for (int k = std::min(2, kmax); k <= kmax; ++k) {
                 const int n = std::max(1, std::min(L.nz, k * cus / tiles));
@@ -1023,8 +1023,28 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
                 if (score > best) {
                     best = score;
                     nzc = n;
+                    kbest = k;
                 }
             }
+            // Several rounds of shorter chunks where no single round fills the
+            // slots: the time of a launch goes as rounds x (planes + 5) x
+            // workgroups per CU, the 5 for a chunk's warm-up.  Measured (us, one
+            // round -> several): 530 x 510 x 280 so 12 float32 (272 tiles, 285
+            // planes -> 40) 366 -> 267, F16 value and difference 374 -> 249, so 8
+            // bfloat16 180 -> 163, float32 279 -> 256; 560 x 592 x 480 so 12 F16
+            // 573 -> 422.  Where a round fills 85 % of the slots or more (every
+            // grid up to 280^3, 592^3) one round was the best or within 3 %, so
+            // the gain has to be 8 % by this estimate.
+            auto cost = [&](int n, int k) {
+                const long long rounds = ((long long)n * tiles + (long long)k * cus - 1) / ((long long)k * cus);
+                return (double)rounds * ((L.nz + n - 1) / n + 5) * k;
+            };
+            double least = 0.92 * cost(nzc, kbest);
+            for (int n = nzc + 1; n <= L.nz; ++n)
+                if (cost(n, kmax) < least) {
+                    least = cost(n, kmax);
+                    nzc = n;
+                }
             // Wide xy planes give long chunks (592^3: 370 tiles, k = 3, two
             // chunks of 296 planes); measured against chunks of 64 planes
             // there, one round of long chunks is as fast in float32 and 3 %
