@@ -686,15 +686,24 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
     // body i of an unrolled group computes from set i mod 3 and issues into
     // set (i + 2) mod 3; UNR is a multiple of 3, so each group starts from
     // the same sets (and, when the queue rotates, from rotation 0)
-    for (; st + UNR <= len; st += UNR)
-        static_for<0, UNR>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            body(I, st + i, set(I), set(std::integral_constant<int, i + 2>{}));
-        });
-    static_for<0, UNR - 1>([&](auto I) {
+    auto plane_step = [&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
-        if (st + i < len) body(I, st + i, set(I), set(std::integral_constant<int, i + 2>{}));
-    });
+        body(I, st + i, set(I), set(std::integral_constant<int, i + 2>{}));
+        return st + i + 1 < len;
+    };
+    if constexpr (kRot && (R == 5 || R == 8)) {
+        // One copy of the long group, left at the chunk's last plane.  With a
+        // second copy for the remaining planes the compiler kept the arrays of
+        // the difference form at radius 8 in scratch memory (336^3 so 16 349 us
+        // per step, 127 now), and the other 16-bit forms at radius 5 and 8 were
+        // up to 9 % slower; at radius 6 and 7 the second copy is 1-3 % faster.
+        while (all_of_seq(std::make_integer_sequence<int, UNR>{}, plane_step)) st += UNR;
+    } else {
+        for (; st + UNR <= len; st += UNR) static_for<0, UNR>(plane_step);
+        static_for<0, UNR - 1>([&](auto I) {
+            if (st + decltype(I)::value < len) plane_step(I);
+        });
+    }
 }
 
 // The 3D step.  SHAPE 16 or 8: every tile has that many float4 columns.
