@@ -1075,18 +1075,9 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
     }
 
     // zero every field (halos included), fill velocity, find v_max
-    hipError_t e = hipSuccess;
-    if ((e = launch_zero_field(L, g->uA, g->st, s)) != hipSuccess ||
-        (e = launch_zero_field(L, g->uB, g->st, s)) != hipSuccess ||
-        ((g->t2 || g->tb2 || g->diff) && (e = launch_zero_field(L, g->uC, g->st, s)) != hipSuccess) ||
-        ((g->t2 || g->tb2) && (e = launch_zero_field(L, g->uD, g->st, s)) != hipSuccess) ||
-        (e = launch_zero_field(L, g->vel, Store::F32, s)) != hipSuccess ||
-        (e = (g->pq ? launch_zero_field(L, g->pq, Store::F16, s) : launch_zero_field(L, g->p, Store::F32, s))) !=
-            hipSuccess)
-        return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
-    for (int i = 0; i < tb2_scratch(g->tb2); ++i)
-        if ((e = launch_zero_field(L, g->ws + wp.scr + wp.field_bytes * (size_t)i, g->st, s)) != hipSuccess)
-            return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
+    // (v, p and every field lie one behind the other: one launch)
+    hipError_t e = launch_zero(g->ws + wp.vel, wp.damp - wp.vel, s);
+    if (e != hipSuccess) return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
     const int phys[3] = {desc->shape[0], desc->ndim == 3 ? desc->shape[1] : 1,
                          desc->ndim == 3 ? desc->shape[2] : desc->shape[1]};
     if ((e = launch_fill_velocity(L, vp_dev, desc->vp_padded, desc->nbl, phys, g->vel, s)) != hipSuccess ||
@@ -1290,9 +1281,7 @@ int fdi_forward_prepare(fd_grid *g, const fd_shot *sh, int nt, double dt, hipStr
 
 // Zero initial state (u^0 = u^{-1} = 0) in uA, uB, and a new run's rows.
 int fdi_forward_zero_state(fd_grid *g, hipStream_t s) {
-    HIPCHK(launch_zero_field(g->L, g->uA, g->st, s));
-    HIPCHK(launch_zero_field(g->L, g->uB, g->st, s));
-    if (g->diff) HIPCHK(launch_zero_field(g->L, g->uC, g->st, s));
+    HIPCHK(launch_zero(g->uA, g->wp.field_bytes * (g->diff ? 3 : 2), s));   // (adjacent)
     g->cur = g->uA;
     g->prev = g->uB;
     g->rows_done = 0;
@@ -1311,19 +1300,20 @@ extern "C" int fd_forward(fd_grid *g, const fd_shot *sh, int nt, double dt, floa
     if ((rc = fdi_forward_prepare(g, sh, nt, dt, s))) return rc;
     if (nt > 0 && sh->nrec > 0 && !rec_out) return fdi_fail(FD_ERR_ARG, "null receiver output");
     const Layout &L = g->L;
-    if (opts && opts->u0) HIPCHK(launch_dense_to_field(L, opts->u0, g->uA, g->st, g->amp, s));
-    else HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-    if (opts && opts->u_prev && !g->diff) HIPCHK(launch_dense_to_field(L, opts->u_prev, g->uB, g->st, g->amp, s));
-    else HIPCHK(launch_zero_field(L, g->uB, g->st, s));
-    if (g->diff) {   // the difference u^0 - u^{-1}, rounded once
-        if (opts && (opts->u0 || opts->u_prev))
+    const size_t fb = g->wp.field_bytes;
+    if (!opts || (!opts->u0 && !opts->u_prev)) {
+        if ((rc = fdi_forward_zero_state(g, s))) return rc;
+    } else {
+        if (opts->u0) HIPCHK(launch_dense_to_field(L, opts->u0, g->uA, g->st, g->amp, s));
+        else HIPCHK(launch_zero(g->uA, fb, s));
+        if (opts->u_prev && !g->diff) HIPCHK(launch_dense_to_field(L, opts->u_prev, g->uB, g->st, g->amp, s));
+        else HIPCHK(launch_zero(g->uB, fb, s));
+        if (g->diff)   // the difference u^0 - u^{-1}, rounded once
             HIPCHK(launch_dense_diff_to_field(L, opts->u0, opts->u_prev, g->uC, g->st, g->amp, s));
-        else
-            HIPCHK(launch_zero_field(L, g->uC, g->st, s));
+        g->cur = g->uA;
+        g->prev = g->uB;
+        g->rows_done = 0;
     }
-    g->cur = g->uA;
-    g->prev = g->uB;
-    g->rows_done = 0;
     if ((rc = fdi_forward_steps(g, sh, nt, 0, nt, rec_out, nullptr, 1, s))) return rc;
     if (opts && opts->save_u) HIPCHK(launch_field_to_dense(L, g->cur, opts->save_u, g->st, 1.f / g->amp, s));
     if (opts && opts->save_u_prev) {
@@ -1352,8 +1342,7 @@ extern "C" int fd_adjoint(fd_grid *g, const fd_shot *sh, int nt, double dt,
     if ((rc = ensure_side(g, 1, sh->nrec, sh->rec_xyz, s))) return rc;
     const Layout &L = g->L;
     note_stream(g, s);
-    HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-    HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+    HIPCHK(launch_zero(g->uA, 2 * g->wp.field_bytes, s));   // uA, uB
     StepArgs a = base_args(g);
     void *A = g->uA, *B = g->uB;   // lambda^k, lambda^{k+1}
     // 16-bit storage keeps amp_adj * lambda.  lambda is of order v^2 r, not
@@ -1559,8 +1548,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         }
         return FD_OK;
     };
-    HIPCHK(launch_zero_f64(gacc, L.elems, s));
-    HIPCHK(launch_zero_field(L, gpart, Store::F32, s));
+    HIPCHK(launch_zero(gacc, gp.rec - gp.grad, s));   // and gpart behind it
 
     if (g->tb2 && !gp.binomial) {
         // 2D, several levels per launch: the fixed-interval schedule below
@@ -1583,11 +1571,9 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         Tb2Run last(g, kBracket, fields, g->cur, g->prev, 0, fwd_inj, 1, sh->nrec, 1.f, s);
         if ((rc = brackets(last, clast, nt, true))) return rc;
         HIPCHK(launch_misfit(recb, d_obs, nres, given, resid, g->partials, kNPart, misfit, s));
-        HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-        HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+        HIPCHK(launch_zero(g->uA, 2 * fb, s));   // uA, uB
         if (clast > 0) {   // (their halo and pad cells are read as zero)
-            HIPCHK(launch_zero_field(L, rotA, g->st, s));
-            HIPCHK(launch_zero_field(L, rotB, g->st, s));
+            HIPCHK(launch_zero(rotA, 2 * fb, s));   // rotA, rotB
         }
         Tb2Run adj(g, kImage, fields, g->uA, g->uB, 1, adj_inj, 0, sh->nsrc, adj_smp, s);
         for (int seg = gp.nseg - 1; seg >= 0; --seg) {
@@ -1617,8 +1603,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         // the bracket of each level (no checkpoint, no recompute), then the
         // residual, then the whole adjoint sweep.
         void *A = rotA, *B = rotB;   // u^n, u^{n-1}
-        HIPCHK(launch_zero_field(L, A, g->st, s));
-        HIPCHK(launch_zero_field(L, B, g->st, s));
+        HIPCHK(launch_zero(rotA, 2 * fb, s));   // rotA, rotB
         for (int n = 0; n < nt; ++n) {
             if ((rc = bracket_step(n, A, B, B, br[n], n >= 1 ? recb + (size_t)(n - 1) * sh->nrec : nullptr)))
                 return rc;
@@ -1627,8 +1612,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         Sample sm = make_sample(g, 1, sh->nrec, recb + (size_t)(nt - 1) * sh->nrec, 1.f);
         HIPCHK(launch_sample(sm, A, g->st, s));
         HIPCHK(launch_misfit(recb, d_obs, nres, given, resid, g->partials, kNPart, misfit, s));
-        HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-        HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+        HIPCHK(launch_zero(g->uA, 2 * fb, s));   // uA, uB
         if ((rc = adjoint_sweep(0, nt))) return rc;
     } else if (!gp.binomial) {
         // 1. forward with checkpoints of (u^c, u^{c-1}) every K steps.  The
@@ -1653,8 +1637,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         //    segment is recomputed from its checkpoint, writing the imaging
         //    bracket of every time level; the adjoint steps read one bracket
         //    per point.
-        HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-        HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+        HIPCHK(launch_zero(g->uA, 2 * fb, s));   // uA, uB
         for (int seg = gp.nseg - 1; seg >= 0; --seg) {
             const int c = seg * K;
             const int e = std::min(c + K, nt);
@@ -1696,11 +1679,9 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
         // samples (a windowed-sinc node outside the grid reads its zero
         // column with weight 0, and 0 times a stale NaN is NaN), and the
         // bracket field.
-        for (int i = 0; i < npool; ++i) HIPCHK(launch_zero_field(L, pool[i], g->st, s));
-        HIPCHK(launch_zero_field(L, out_f, g->st, s));
-        HIPCHK(launch_zero_field(L, brf, Store::F32, s));
-        HIPCHK(launch_zero_field(L, g->uA, g->st, s));
-        HIPCHK(launch_zero_field(L, g->uB, g->st, s));
+        // (checkpoint pairs, rotating pair and brackets lie one behind the other)
+        HIPCHK(launch_zero(ws + gp.ckpt, gp.grad - gp.ckpt, s));
+        HIPCHK(launch_zero(g->uA, 2 * fb, s));   // uA, uB
         slot_u[0] = cu;
         slot_p[0] = cp;
         ref[cu] = ref[cp] = 1;

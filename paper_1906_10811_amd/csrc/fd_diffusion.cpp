@@ -90,8 +90,8 @@ int run_diffusion(const fd_diffusion_desc *desc, void *workspace, size_t ws_byte
     }
     const float w0 = (float)(k * (c[0] / hx2 + c[0] / hy2));
     hipError_t e;
-    if ((e = launch_zero_field(L, A, Store::F32, s)) != hipSuccess ||
-        (e = launch_zero_field(L, B, Store::F32, s)) != hipSuccess ||
+    // (every grid cell of A is written here, of B by the first launch)
+    if ((e = launch_zero_rim2d(L, A, s)) != hipSuccess || (e = launch_zero_rim2d(L, B, s)) != hipSuccess ||
         (e = launch_dense_to_field(L, u0, A, Store::F32, 1.f, s)) != hipSuccess)
         return fdi_fail(FD_ERR_DEVICE, "diffusion setup: %s", hipGetErrorString(e));
     // temporal blocking: each launch advances several levels (the thesis's OPS

@@ -229,7 +229,10 @@ hipError_t launch_make_p(const Layout &L, const float *vel, double dt, float *p,
 // code = nearest integer in [0, 65535] to (dt^2 v^2 - base) / step, float64
 hipError_t launch_make_pq(const Layout &L, const float *vel, double dt, double base, double step,
                           uint16_t *pq, hipStream_t s);
-hipError_t launch_zero_field(const Layout &L, void *f, Store st, hipStream_t s);
+// `bytes` zero bytes (a multiple of 16) at a 16-byte aligned address.
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
+// Zero the pads and halo rows of a 2D float32 field, not its grid quads.
+hipError_t launch_zero_rim2d(const Layout &L, float *f, hipStream_t s);
 hipError_t launch_dense_to_field(const Layout &L, const float *dense, void *f, Store st,
                                  float scale, hipStream_t s);
 hipError_t launch_field_to_dense(const Layout &L, const void *f, float *dense, Store st,
@@ -252,7 +255,6 @@ hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w
 hipError_t static_scratch(int device, void **ptr);
 hipError_t launch_misfit(const float *rec, const float *obs, long long n, int residual_given,
                          float *resid, double *partials, int npart, double *out, hipStream_t s);
-hipError_t launch_zero_f64(double *p, long long n, hipStream_t s);
 // acc += part; part = 0 over the grid rows of two pitched fields of layout L
 // (float64 and float32); halo and pad cells are not touched.
 hipError_t launch_fold_f64(const Layout &L, double *acc, float *part, hipStream_t s);
