@@ -752,6 +752,7 @@ Inject make_inject(const fd_grid *g, int side, const float *vals, float scale) {
     in.w = d.ent_w;
     in.vals = (g->ncorner[side] > 0) ? vals : nullptr;
     in.scale = scale;
+    in.one_entry = g->one_entry[side];
     return in;
 }
 
@@ -1217,9 +1218,9 @@ int fdi_forward_steps(fd_grid *g, const fd_shot *sh, int nt, int n0, int n1, flo
             const SparseDev &d = g->sd[0];
             const bool any = g->ncorner[0] > 0;
             t.inj = Inject{g->t2_pp, g->t2_corner, d.ent_src, d.ent_w,
-                           any ? sh->src_wavelet + (size_t)n * sh->nsrc : nullptr, inj_scale};
+                           any ? sh->src_wavelet + (size_t)n * sh->nsrc : nullptr, inj_scale, 0};
             t.inj2 = Inject{g->t2_pp, g->t2_corner, d.ent_src, d.ent_w,
-                            any ? sh->src_wavelet + (size_t)(n + 1) * sh->nsrc : nullptr, inj_scale};
+                            any ? sh->src_wavelet + (size_t)(n + 1) * sh->nsrc : nullptr, inj_scale, 0};
             t.smp = make_sample(g, 1, sh->nrec, row(n - 1), smp_scale);
             t.nsamp_blocks = samp_blocks(t.smp);
             t.smp2 = make_sample(g, 1, sh->nrec, row(n - 2), smp_scale);

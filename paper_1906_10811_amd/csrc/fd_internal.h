@@ -69,6 +69,7 @@ struct Inject {
     const float *w;         // entry -> interpolation weight
     const float *vals;      // this step's row of values, nullptr = no injection
     float scale;            // multiplies every value
+    int one_entry;          // every corner has one entry, of its own index
 };
 
 // Sampling of the centre field at sparse points by extra workgroups: `lpp`

@@ -184,7 +184,10 @@ __device__ inline void scatter_sources(const Inject &inj, int e0, int e1, int x0
     for (int e = e0 + (int)threadIdx.x; e < e1; e += kBlock) {
         const int4 c = inj.corner[e];
         float v = 0.f;
-        for (int k = c.z; k < c.w; ++k) v = __builtin_fmaf(inj.w[k], inj.vals[inj.src[k]], v);
+        if (inj.one_entry)   // entry e is corner e's only one: no wait for its range
+            v = __builtin_fmaf(inj.w[e], inj.vals[inj.src[e]], v);
+        else
+            for (int k = c.z; k < c.w; ++k) v = __builtin_fmaf(inj.w[k], inj.vals[inj.src[k]], v);
         s_src[(c.y - y0) * TX + (c.x - x0)] = v * inj.scale;
     }
 }
