@@ -219,6 +219,22 @@ def _vs_fp64(got, want):
     return float(np.linalg.norm(g - want) / np.linalg.norm(want))
 
 
+def _adjoint_bytes(nt, K):
+    """Algorithmic bytes per point of an adjoint step, over the reverse sweep
+    in segments of K: three steps at a time where a segment and the 32 steps
+    between folds have room (16 each, three brackets read, one partial-sum
+    read-modify-write: 68), else 16 + 4 + 8."""
+    total, done, e = 0.0, 0, nt
+    while e > 0:
+        c = (e - 1) // K * K
+        while e > c:
+            n = 3 if e - c >= 3 and 32 - done % 32 >= 3 else 1
+            total += 68.0 if n == 3 else 28.0
+            done += n
+            e -= n
+    return total / nt
+
+
 def bench_gradient(torch, dev, stream):
     """fd_gradient on gradient3d_200: forward with checkpoints every 50 steps,
     residual and FP64 misfit, segment recompute, adjoint with fused imaging;
@@ -248,16 +264,16 @@ def bench_gradient(torch, dev, stream):
     secs = e0.elapsed_time(e1) / 1000.0 / reps
     # algorithmic bytes per point and time step: forward 16 (20 with the
     # bracket write in the last segment), recompute of the other segments
-    # 16 + bracket write 4, adjoint 16 + bracket read 4 + float32 partial-sum
-    # read-modify-write 8, the fold into the float64 gradient (read 4, RMW 16,
-    # clear 4) every 32 adjoint steps, and two field copies (read + write)
-    # per checkpoint (none for the last segment; a segment is recomputed in
-    # its checkpoint's own fields)
+    # 16 + bracket write 4, adjoint steps as _adjoint_bytes has them, the fold
+    # into the float64 gradient (read 4, RMW 16, clear 4) every 32 adjoint
+    # steps, and two field copies (read + write) per checkpoint (none for the
+    # last segment; a segment is recomputed in its checkpoint's own fields)
     K = w["checkpoint_every"]
     nt = w["nt"]
     nseg = -(-nt // K)
     last = nt - (nseg - 1) * K
-    b_alg = 16.0 + 4.0 * last / nt + 20.0 * (nt - last) / nt + 28.0 + 24.0 / 32 + 16.0 * (nseg - 1) / nt
+    b_alg = 16.0 + 4.0 * last / nt + 20.0 * (nt - last) / nt + _adjoint_bytes(nt, K) + 24.0 / 32 \
+        + 16.0 * (nseg - 1) / nt
     gpts = g.padded_points * w["nt"] / secs / 1e9
     out = dict(workload="gradient3d_200", gpts=gpts, ms=secs * 1000.0, misfit=float(mis.item()),
                checkpoint_every=K, b_alg_per_pt=b_alg, achieved_gbs=gpts * b_alg,
@@ -265,7 +281,7 @@ def bench_gradient(torch, dev, stream):
                workspace_gb=g.gradient_workspace_bytes(w["nt"], len(w["rec"]), checkpoint_every=K) / 1e9)
     # every bracket resident (checkpoint_every >= nt: 800 FP32 fields of 280^3
     # fit in HBM): the forward pass writes the brackets, nothing is
-    # recomputed; bytes per point and step 20 + 28 + 24/32
+    # recomputed; bytes per point and step 20, the adjoint steps' and 24/32
     with torch.cuda.stream(stream):
         g.gradient(w["src"], wav, w["rec"], d_obs, w["dt"], checkpoint_every=w["nt"], stream=stream)
         torch.cuda.synchronize()
@@ -275,7 +291,7 @@ def bench_gradient(torch, dev, stream):
     torch.cuda.synchronize()
     sa = e0.elapsed_time(e1) / 1000.0
     ga = g.padded_points * w["nt"] / sa / 1e9
-    ba = 48.0 + 24.0 / 32
+    ba = 20.0 + _adjoint_bytes(w["nt"], w["nt"]) + 24.0 / 32
     out["all_brackets_resident"] = dict(
         ms=sa * 1000.0, gpts=ga, b_alg_per_pt=ba, frac_hbm=ga * ba / HBM_PEAK_GBS,
         misfit_equal=bool(float(misa.item()) == float(mis.item())),
@@ -515,9 +531,9 @@ def bench_diffusion(torch, dev, stream):
             torch.cuda.synchronize()
             secs = e0.elapsed_time(e1) / 1000.0
             gpts = n * n * 1000 / secs / 1e9
-            # the library's automatic choice: temporally blocked (8 B per point
-            # per launch of lev steps) at so 2, 4 and 8, one step per launch otherwise
-            lev = {1: 8, 2: 8, 4: 4}.get(r, 1)
+            # the library's automatic choice: several levels per launch (8 B per
+            # point and launch of lev steps)
+            lev = {2500: {1: 8, 2: 4, 4: 2, 6: 2}, 10000: {1: 8, 2: 8, 4: 4, 6: 2}}[n][r]
             diffusion(u0, (h, h), so, 0.5, dt, 10, out=res, stream=stream, time_block=0)
             torch.cuda.synchronize()
             with torch.cuda.stream(stream):
