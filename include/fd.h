@@ -458,7 +458,7 @@ int fd_diffusion_run(const fd_diffusion_desc *desc, void *workspace, size_t ws_b
  * array of 64 MiB inside the library, one per GPU, held until the process
  * ends; nothing is allocated or freed.  Grids whose two pitched fields
  * exceed it (beyond about 2800 x 2800) give FD_ERR_NOMEM.  Every call on a
- * GPU uses that GPU's one array: the call clears it before use, and calls
+ * GPU uses that GPU's one array: nothing in it outlives a call, and calls
  * that overlap in time on one GPU (two streams, two threads) race -- order
  * them.  The first call on a device resolves the array's address there.
  * Arguments, result and errors otherwise as fd_diffusion_run.

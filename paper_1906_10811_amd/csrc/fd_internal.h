@@ -16,9 +16,9 @@ constexpr int kTile2Z = 64;       // z rows per 2D tile
 constexpr int kBlock = 256;       // threads per workgroup
 constexpr int kMaxChunk = 512;    // z planes per 3D workgroup at most
 // Largest field whose new time level a step stores with ordinary stores
-// rather than non-temporal ones (16-bit 3D fields, 2D diffusion fields): a
-// field this small can still sit in the 256 MB memory-side cache when the
-// next step reads it.
+// rather than non-temporal ones (16-bit 3D fields, 2D diffusion fields), and
+// largest float32 p a 3D step reads with ordinary loads: a field this small
+// can still sit in the 256 MB memory-side cache when the next step reads it.
 constexpr size_t kCachedField = size_t(128) << 20;
 // Bytes of the static device scratch behind fd_diffusion_run_noalloc (two
 // pitched float32 fields: a 2500 x 2500 grid at every space order).

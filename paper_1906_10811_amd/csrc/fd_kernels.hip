@@ -3,7 +3,8 @@
 // The hot loop is the per-step space loop of an explicit finite-difference
 // stepper (the thesis launches one data-parallel loop per time step from a
 // host time loop, Section 3.3.3 "Parallel loop invocation"); here one launch
-// of k_step3d / k_step2d performs the whole step:
+// of k_step3d / k_step2d performs the whole step (several 2D steps per launch
+// are in fd_step2d.hip, the diffusion operator is in fd_diffuse2d.hip):
 //
 //   lap  = w0 u + sum_j wx_j (u_{x+j} + u_{x-j}) + wy_j (..) + wz_j (..)
 //   s    = sigma dt / 2                     (per-axis tables, 0 off the layer)
@@ -15,8 +16,8 @@
 // the inner loop: the lesson of the aggressive-DSE kernel of Section 5.1.5).
 //
 // 3D: 2.5D blocking.  A workgroup owns a 64 x 16 or a 32 x 32 xy tile and
-// marches a chunk of z planes.  Each lane keeps 4 consecutive x points and a register queue
-// of the 2r+1 z values of its column; the current xy plane (tile + r halo) is
+// marches a chunk of z planes.  Each lane keeps 4 consecutive x points and a
+// register queue of the 2r+1 z values of its column; the current xy plane (tile + r halo) is
 // staged through LDS (double-buffered, one barrier per plane) for the x and y
 // neighbours.  Loads of plane z+1 are issued before plane z is computed.
 // Arithmetic is FP32 whatever the storage type.  No MFMA: the update is a
