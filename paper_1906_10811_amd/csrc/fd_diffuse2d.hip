@@ -32,7 +32,7 @@ struct DiffArgs {
     float w0;
     float wx[kMaxR + 1];
     float wz[kMaxR + 1];
-    int nstrip;       // strips, or tiles along x
+    int nstrip;       // strips or tiles along x
     int chunk;        // strips: rows per wave
     int nlev;         // levels of this launch
     int out_cached;   // ordinary stores of the new level (small fields), else non-temporal
@@ -137,6 +137,54 @@ __global__ __launch_bounds__(kNT) void k_diffuse2d_tile(const DiffArgs a) {
 #pragma unroll
     for (int k = 0; k < kK; ++k)
         if (mine[k]) *reinterpret_cast<float4 *>(a.out + off[k]) = u[k];
+}
+
+// One level: a 64 x 64 tile staged with its R halo; each lane updates 4 points
+// in each of 4 rows.  Rows are written as whole cache lines, which a strip
+// (256 points less its halo) cannot: where one level per launch streams from
+// HBM and the arithmetic is short, that decides.
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_diffuse2d_one(const DiffArgs a) {
+    constexpr int HX4 = (R + 3) / 4;
+    constexpr int W4 = kTileX / 4 + 2 * HX4;
+    constexpr int LH = kTile2Z + 2 * R;
+    __shared__ float4 lds[LH * W4];
+    const Layout L = a.L;
+    const int t = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+    const int x0 = (t % a.nstrip) * kTileX, z0 = (t / a.nstrip) * kTile2Z;
+    const int lane = (int)threadIdx.x;
+    const long long zcol = L.offset((L.nx + 3) & ~3, 0, 0);   // zero
+    for (int i = lane; i < LH * W4; i += kBlock) {
+        const int lr = i / W4, c = i - lr * W4;
+        const int gz = z0 - R + lr, gx = x0 - 4 * HX4 + 4 * c;
+        const bool ok = gz >= 0 && gz < L.nz && gx >= 0 && gx < L.nx;
+        lds[i] = *reinterpret_cast<const float4 *>(a.u + (ok ? L.offset(gx, 0, gz) : zcol));
+    }
+    __syncthreads();
+    const int tx = lane % (kTileX / 4), tz = lane / (kTileX / 4);
+    const int x = x0 + 4 * tx;
+    if (x >= L.nx) return;
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+        const int z = z0 + tz * 4 + rr;
+        if (z >= L.nz) break;
+        const float4 *row = lds + (R + tz * 4 + rr) * W4 + HX4 + tx;
+        float xs[4 * (2 * HX4 + 1)], un[4];
+#pragma unroll
+        for (int c = -HX4; c <= HX4; ++c) put4(xs + 4 * (c + HX4), row[c]);
+        diffuse4<R, HX4>(a, xs, [&](int j) { return row[j * W4]; }, [&](int j) { return row[-j * W4]; }, un);
+        if (x + 4 > L.nx) {   // (the cells past nx of a row's last group must be zero)
+#pragma unroll
+            for (int i = 1; i < 4; ++i)
+                if (x + i >= L.nx) un[i] = 0.f;
+        }
+        float *o = a.out + L.offset(x, 0, z);
+        const float4 v = make_float4(un[0], un[1], un[2], un[3]);
+        if (a.out_cached)
+            *reinterpret_cast<float4 *>(o) = v;
+        else
+            st4nt_f32(o, v);
+    }
 }
 
 template <int R, int T>
@@ -290,6 +338,20 @@ DiffFn tile_kernel(int r) {
     return nullptr;
 }
 
+DiffFn one_kernel(int r) {
+    switch (r) {
+        case 1: return k_diffuse2d_one<1>;
+        case 2: return k_diffuse2d_one<2>;
+        case 3: return k_diffuse2d_one<3>;
+        case 4: return k_diffuse2d_one<4>;
+        case 5: return k_diffuse2d_one<5>;
+        case 6: return k_diffuse2d_one<6>;
+        case 7: return k_diffuse2d_one<7>;
+        case 8: return k_diffuse2d_one<8>;
+    }
+    return nullptr;
+}
+
 // Which kernel and how many levels, measured per step at every order, level
 // count and kernel on 203 x 141, 500^2, 1000^2, 10000 x 300, 300 x 10000, 2500^2,
 // 4000^2 and 10000^2 (float32, us; the former kernels, 64 x 64 tiles in LDS,
@@ -300,9 +362,10 @@ DiffFn tile_kernel(int r) {
 //   2500^2                       3.28 / 3.75   4.95 / 5.71   8.27 / 8.65   14.1 / 11.4   (7.3 8.4 12.4 15.7)
 //   10000^2                      46.4 / 33.6   74.3 / 52.0   128 / 84.8    213 / 110     (85 97 143 174)
 // The strips win once they fill the GPU: above 7 M points up to radius 4, 4 M
-// at radius 5 and 6, 2 M beyond.
-bool use_tiles(const Layout &L) {
+// at radius 5 and 6, 2 M beyond; single levels at radius 1 and 2 above 4 M.
+bool use_tiles(const Layout &L, int most) {
     const long long n = (long long)L.nx * L.nz;
+    if (most == 1 && L.r <= 2) return n <= 4000000;
     return n <= (L.r <= 4 ? 7000000 : L.r <= 6 ? 4000000 : 2000000);
 }
 
@@ -326,13 +389,15 @@ int tile_levels(const Layout &L) {
 
 // Strips: one round of two waves per SIMD (three or four measured no faster on
 // the largest grids, up to 30 % slower on 2500^2, as each wave recomputes 2 R T
-// rows).  With C rows per wave, T levels pay while C is large against that:
+// rows; but a single level at radius 1 or 2 recomputes little and waits on
+// memory: 16384 waves, 4000^2 so 2 / 4 21.3 / 22.5 -> 20.2 / 20.6 us).  With C rows per wave, T levels pay while C is large against that:
 // measured, C >= R T for two levels, about (R T)^2 / 6.4 for more.
 constexpr int kWaves = 2048, kMinRows = 8;
 void strip_shape(const Layout &L, int lev, int *nstrip, int *chunk) {
     const int HX = (L.r * lev + 3) & ~3;
     *nstrip = (L.nx + kStrip - 2 * HX - 1) / (kStrip - 2 * HX);
-    const int chunks = std::max(1, std::min(kWaves / *nstrip, L.nz / kMinRows));
+    const int waves = lev == 1 && L.r <= 2 ? 8 * kWaves : kWaves;
+    const int chunks = std::max(1, std::min(waves / *nstrip, L.nz / kMinRows));
     *chunk = (L.nz + chunks - 1) / chunks;
 }
 int strip_levels(const Layout &L, int most) {
@@ -344,6 +409,24 @@ int strip_levels(const Layout &L, int most) {
         if (lev == 2 ? chunk >= h : 64 * (long long)chunk >= 10 * h * h) return lev;
     }
     return 1;
+}
+
+// One level per launch (asked for, or the last of a count).  Measured (us):
+//                       so 2          so 4          so 8   so 16
+//   10000^2, strips       176 (162)     177 (163)     172    177     (16384 waves)
+//            this kernel  150           151           158    173
+//   2500^2,  tiles        10.2          10.6          11.6   19.6
+//            strips       -- (9.2)      -- (9.6)      --     15.5
+//            this kernel  10.0          10.4          11.8   15.9
+//   3000^2,  strips       12.5 (12.0)   14.0 (12.3)   15.3   20.4
+//            this kernel  13.4          13.8          15.6   18.2
+// So: fields beyond the memory-side cache's reach take this kernel; others
+// take it where the strips' 2 R recomputed rows weigh (radius 8, up to 20 M
+// points: 4000^2 29.6 and 29.4, 5000^2 41.2 and 43.3) and at radius 4 on the
+// largest grids of tiles (2600^2 13.1 against 12.2).
+bool use_one(const Layout &L, bool cached, bool tiles) {
+    const long long n = (long long)L.nx * L.nz;
+    return !cached || (tiles ? L.r == 4 && n > 6500000 : L.r == 8 && n <= 20000000);
 }
 
 }  // namespace
@@ -361,13 +444,16 @@ hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w
         a.wz[j] = wz[j];
     }
     a.out_cached = (size_t)L.elems * sizeof(float) <= kCachedField;
-    if (use_tiles(L)) {
-        a.nlev = std::min(most, tile_levels(L));
+    const bool tiles = use_tiles(L, most);
+    a.nlev = tiles ? std::min(most, tile_levels(L)) : strip_levels(L, most);
+    if (a.nlev == 1 && use_one(L, a.out_cached, tiles)) {
+        a.nstrip = (L.nx + kTileX - 1) / kTileX;
+        hipLaunchKernelGGL(one_kernel(L.r), dim3(a.nstrip * ((L.nz + kTile2Z - 1) / kTile2Z)), dim3(kBlock), 0, s, a);
+    } else if (tiles) {
         int ntz;
         tile_shape(L, a.nlev, &a.nstrip, &ntz);
         hipLaunchKernelGGL(tile_kernel(L.r), dim3(a.nstrip * ntz), dim3(kNT), 0, s, a);
     } else {
-        a.nlev = strip_levels(L, most);
         strip_shape(L, a.nlev, &a.nstrip, &a.chunk);
         hipLaunchKernelGGL(strip_kernel(L.r, a.nlev), dim3(a.nstrip * ((L.nz + a.chunk - 1) / a.chunk)), dim3(64), 0,
                            s, a);
