@@ -143,8 +143,9 @@ __global__ __launch_bounds__(kNT) void k_diffuse2d_tile(const DiffArgs a) {
 // in each of 4 rows.  Rows are written as whole cache lines, which a strip
 // (256 points less its halo) cannot: where one level per launch streams from
 // HBM and the arithmetic is short, that decides.
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_diffuse2d_one(const DiffArgs a) {
+// WAVES bounds the waves per SIMD the compiler plans registers for.
+template <int R, int WAVES = 8>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void k_diffuse2d_one(const DiffArgs a) {
     constexpr int HX4 = (R + 3) / 4;
     constexpr int W4 = kTileX / 4 + 2 * HX4;
     constexpr int LH = kTile2Z + 2 * R;
@@ -338,7 +339,7 @@ DiffFn tile_kernel(int r) {
     return nullptr;
 }
 
-DiffFn one_kernel(int r) {
+DiffFn one_kernel(int r, bool cached) {
     switch (r) {
         case 1: return k_diffuse2d_one<1>;
         case 2: return k_diffuse2d_one<2>;
@@ -347,7 +348,9 @@ DiffFn one_kernel(int r) {
         case 5: return k_diffuse2d_one<5>;
         case 6: return k_diffuse2d_one<6>;
         case 7: return k_diffuse2d_one<7>;
-        case 8: return k_diffuse2d_one<8>;
+        // (five waves' registers hide the reads of a cached field better, 2500^2 15.9
+        // -> 15.3 us, and lose 12 % on 10000^2)
+        case 8: return cached ? k_diffuse2d_one<8, 5> : k_diffuse2d_one<8>;
     }
     return nullptr;
 }
@@ -391,7 +394,9 @@ int tile_levels(const Layout &L) {
 // the largest grids, up to 30 % slower on 2500^2, as each wave recomputes 2 R T
 // rows; but a single level at radius 1 or 2 recomputes little and waits on
 // memory: 16384 waves, 4000^2 so 2 / 4 21.3 / 22.5 -> 20.2 / 20.6 us).  With C rows per wave, T levels pay while C is large against that:
-// measured, C >= R T for two levels, about (R T)^2 / 6.4 for more.
+// measured, C >= R T for two levels, about (R T)^2 / 6.4 for more; radius 8
+// takes two only beyond the memory-side cache's reach (6500^2 68 us a step
+// against 79; 4000^2 31.0 against 30.5, 5000^2 44.1 against 41.6).
 constexpr int kWaves = 2048, kMinRows = 8;
 void strip_shape(const Layout &L, int lev, int *nstrip, int *chunk) {
     const int HX = (L.r * lev + 3) & ~3;
@@ -400,10 +405,10 @@ void strip_shape(const Layout &L, int lev, int *nstrip, int *chunk) {
     const int chunks = std::max(1, std::min(waves / *nstrip, L.nz / kMinRows));
     *chunk = (L.nz + chunks - 1) / chunks;
 }
-int strip_levels(const Layout &L, int most) {
+int strip_levels(const Layout &L, int most, bool cached) {
     for (int lev = 8; lev > 1; lev /= 2) {
         const long long h = (long long)L.r * lev;
-        if (lev > most || h > kDiffHalo) continue;
+        if (lev > most || h > kDiffHalo || (L.r == 8 && cached)) continue;
         int nstrip, chunk;
         strip_shape(L, lev, &nstrip, &chunk);
         if (lev == 2 ? chunk >= h : 64 * (long long)chunk >= 10 * h * h) return lev;
@@ -417,12 +422,12 @@ int strip_levels(const Layout &L, int most) {
 //            this kernel  150           151           158    173
 //   2500^2,  tiles        10.2          10.6          11.6   19.6
 //            strips       -- (9.2)      -- (9.6)      --     15.5
-//            this kernel  10.0          10.4          11.8   15.9
+//            this kernel  10.0          10.4          11.8   15.3
 //   3000^2,  strips       12.5 (12.0)   14.0 (12.3)   15.3   20.4
-//            this kernel  13.4          13.8          15.6   18.2
+//            this kernel  13.4          13.8          15.6   18.8
 // So: fields beyond the memory-side cache's reach take this kernel; others
 // take it where the strips' 2 R recomputed rows weigh (radius 8, up to 20 M
-// points: 4000^2 29.6 and 29.4, 5000^2 41.2 and 43.3) and at radius 4 on the
+// points; 5000^2 41.2 by strips, 43.3) and at radius 4 on the
 // largest grids of tiles (2600^2 13.1 against 12.2).
 bool use_one(const Layout &L, bool cached, bool tiles) {
     const long long n = (long long)L.nx * L.nz;
@@ -445,10 +450,10 @@ hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w
     }
     a.out_cached = (size_t)L.elems * sizeof(float) <= kCachedField;
     const bool tiles = use_tiles(L, most);
-    a.nlev = tiles ? std::min(most, tile_levels(L)) : strip_levels(L, most);
+    a.nlev = tiles ? std::min(most, tile_levels(L)) : strip_levels(L, most, a.out_cached);
     if (a.nlev == 1 && use_one(L, a.out_cached, tiles)) {
         a.nstrip = (L.nx + kTileX - 1) / kTileX;
-        hipLaunchKernelGGL(one_kernel(L.r), dim3(a.nstrip * ((L.nz + kTile2Z - 1) / kTile2Z)), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(one_kernel(L.r, a.out_cached), dim3(a.nstrip * ((L.nz + kTile2Z - 1) / kTile2Z)), dim3(kBlock), 0, s, a);
     } else if (tiles) {
         int ntz;
         tile_shape(L, a.nlev, &a.nstrip, &ntz);
