@@ -819,6 +819,7 @@ public:
         a.nsamp_blocks = pend_.nrows * pend_.bpr;
         const bool smp = out && npts_ > 0;
         a.node_pp = smp ? g_->sd[smp_].plane_ptr : nullptr;
+        a.node_reach = g_->d.sinc_radius > 0 ? 2 * g_->d.sinc_radius - 1 : 1;   // nodes per axis, less one
         SampleRows next{};
         for (int t = 0; t < nlev; ++t) {
             void *lev = t == nlev - 1   ? f[0]

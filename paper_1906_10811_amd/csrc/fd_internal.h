@@ -190,9 +190,11 @@ struct Step2Args {
     float scale;
     int one_entry;                // every injected point has one entry, of its own index
     // sampling: tiles with points of node_pp (per-column plane pointers; null:
-    // none) store level t + 1 < n + nlev - 1 in lev_out[t]; smp are the rows of
-    // the launch before, sampled by nsamp_blocks trailing workgroups
+    // none), or within node_reach points of one, store level t + 1 < n + nlev -
+    // 1 in lev_out[t]; smp are the rows of the launch before, sampled by
+    // nsamp_blocks trailing workgroups
     const int *node_pp;
+    int node_reach;
     void *lev_out[kTb2MaxLev];
     SampleRows smp;
     int nsamp_blocks;

@@ -155,16 +155,21 @@ __global__ __launch_bounds__(kNT) void k_step2d_tb(const Step2Args a) {
             s_val[t * kSrcCap + j] = src_val(e, t);
         }
 
-    // whether the tile holds points that are sampled (its intermediate levels
-    // are then stored for the next launch's sampling)
+    // Whether the tile holds points that are sampled (its intermediate levels
+    // are then stored for the next launch's sampling).  The tables leave out
+    // nodes of weight zero, which are read all the same (0 times what an
+    // earlier run left there may be NaN): every node lies within node_reach of
+    // one that the tables have.
     bool nodes = false;
-    const int xu0 = max(x0 + Hx, 0), xu1 = min(x0 + 4 * kW4 - Hx, L.nx) - 1;
-    const int zu0 = z0 + H, zu1 = min(z0 + kRows - H, L.nz);
-    if (a.node_pp)
+    if (a.node_pp) {
+        const int n = a.node_reach;
+        const int xu0 = max(x0 + Hx - n, 0), xu1 = min(x0 + 4 * kW4 - Hx + n, L.nx) - 1;
+        const int zu0 = max(z0 + H - n, 0), zu1 = min(z0 + kRows - H + n, L.nz);
         for (int ct = xu0 / kTileX; ct <= xu1 / kTileX; ++ct) {
             const int *q = a.node_pp + (long long)ct * (L.nz + 1);
             nodes |= q[zu0] < q[zu1];
         }
+    }
     // the lane's quads that are this tile's to write
     bool mine[kK];
 #pragma unroll
