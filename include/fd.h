@@ -148,8 +148,10 @@ typedef struct fd_grid_desc {
                               to 1 GiB per field run up to 8 levels per launch, chosen by
                               radius and grid size, in fd_forward, fd_adjoint and
                               fd_gradient's fixed-interval schedules, with two more
-                              wavefield buffers and 2 (levels - 2) scratch ones in the
-                              workspace; results are bitwise those of 1); anything
+                              wavefield buffers and 2 (levels - 2) scratch ones, of at
+                              most 2 GiB together, in the workspace; results are bitwise
+                              those of 1, and a workspace of the size that 1 needs is
+                              accepted and selects it); anything
                               else, or 2 where it is not available, is FD_ERR_ARG.
                               Served 2D shots run one step per launch */
     int param_storage;     /* fd_param_storage; FD_PARAM_Q16 in 3D only */
@@ -267,7 +269,8 @@ int fd_adjoint(fd_grid *grid, const fd_shot *shot, int nt, double dt,
  * every checkpoint_every steps except the last segment's (ceil(nt /
  * checkpoint_every) - 1 pairs) and checkpoint_every bracket fields of the
  * segment recompute (and two more fields on 2D grids that run several levels
- * per launch); with checkpoint_every >= nt, nt bracket fields and no
+ * per launch; fd_gradient also accepts a workspace without them and then runs
+ * one step per launch); with checkpoint_every >= nt, nt bracket fields and no
  * checkpoint (the forward pass keeps every bracket, nothing is recomputed).
  * FD_GRAD_BINOMIAL: checkpoint_every + 1 snapshots and two scratch fields.
  * All add the float64 gradient, its float32 partial sum, traces and

@@ -232,20 +232,26 @@ bool t2_enabled(const fd_grid_desc *d) {
     return avail && (d->time_block == 2 || (d->time_block == 0 && d->space_order == 2));
 }
 
+// Scratch fields of a launch of several 2D levels: the levels it neither
+// starts from nor ends with, twice (a launch samples those of the one before).
+inline int tb2_scratch(int levels) { return levels > 2 ? 2 * (levels - 2) : 0; }
+
 // Levels per launch of a 2D grid's forward, adjoint and gradient steps
 // (k_step2d_tb; 0: one step per launch, k_step2d).  The automatic choice;
 // time_block 1 asks for one step per launch.  The levels need two more state
-// fields and, beyond two levels, scratch fields for the sampled levels, so
-// grids of more than kTb2MaxField bytes per field keep two fields.
-constexpr size_t kTb2MaxField = size_t(1) << 30;
+// fields and, beyond two levels, scratch fields for the sampled levels: grids
+// of more than kTb2MaxField bytes per field keep two fields, and the scratch
+// is bounded by fewer levels (a 432 MB field at so 2, 12000 x 9000: four
+// levels instead of eight, 124 us per step; one step per launch 316).
+constexpr size_t kTb2MaxField = size_t(1) << 30, kTb2MaxScratch = size_t(2) << 30;
 int tb2_levels(const fd_grid_desc *d, const Layout &L) {
     if (d->ndim != 2 || d->time_block != 0) return 0;
-    if ((size_t)L.elems * (d->storage == FD_STORE_F32 ? 4 : 2) > kTb2MaxField) return 0;
-    return step2d_levels(L);
+    const size_t field = (size_t)L.elems * (d->storage == FD_STORE_F32 ? 4 : 2);
+    if (field > kTb2MaxField) return 0;
+    int lev = step2d_levels(L);
+    while (field * tb2_scratch(lev) > kTb2MaxScratch) --lev;
+    return lev;
 }
-// Scratch fields of those levels: the levels a launch neither starts from nor
-// ends with, twice (a launch samples those of the one before it).
-inline int tb2_scratch(int levels) { return levels > 2 ? 2 * (levels - 2) : 0; }
 
 // 16-bit value-and-difference storage, and the element type of a storage.
 inline bool diff_storage(const fd_grid_desc *d) {
@@ -911,7 +917,13 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
     if (!workspace || !vp_dev) return fdi_fail(FD_ERR_ARG, "null workspace or velocity");
     if ((uintptr_t)workspace % 256) return fdi_fail(FD_ERR_ARG, "workspace must be 256-byte aligned");
     const Layout L = fdi_layout(desc);
-    const WsPlan wp = plan(desc, L);
+    WsPlan wp = plan(desc, L);
+    fd_grid_desc one_step = *desc;
+    if (ws_bytes < wp.total && tb2_levels(desc, L)) {   // too small for the levels: one step per launch
+        one_step.time_block = 1;
+        desc = &one_step;
+        wp = plan(desc, L);
+    }
     if (ws_bytes < wp.total)
         return fdi_fail(FD_ERR_NOMEM, "workspace %zu bytes < required %zu", ws_bytes, wp.total);
     hipStream_t s = (hipStream_t)stream;
@@ -1077,8 +1089,13 @@ extern "C" int fd_grid_create(const fd_grid_desc *desc, void *workspace, size_t 
     }
 
     // zero every field (halos included), fill velocity, find v_max
-    // (v, p and every field lie one behind the other: one launch)
-    hipError_t e = launch_zero(g->ws + wp.vel, wp.damp - wp.vel, s);
+    // (v, p and every field lie one behind the other: one launch).  Of the
+    // scratch fields only the cells read for nodes outside the grid: every
+    // other one that is read was written by the same run.
+    const size_t esz = g->st == Store::F32 ? 4 : 2;
+    hipError_t e = launch_zero_and_quads(g->ws + wp.vel, wp.scr - wp.vel,
+                                         g->ws + wp.scr + L.offset((L.nx + 3) & ~3, 0, 0) * esz, wp.field_bytes,
+                                         tb2_scratch(g->tb2), g->st, s);
     if (e != hipSuccess) return cleanup(fdi_fail(FD_ERR_DEVICE, "zero fill: %s", hipGetErrorString(e)));
     const int phys[3] = {desc->shape[0], desc->ndim == 3 ? desc->shape[1] : 1,
                          desc->ndim == 3 ? desc->shape[2] : desc->shape[1]};
@@ -1399,7 +1416,7 @@ struct GradPlan {
     int ncp, nseg, K, nbr;   // checkpoint pairs (binomial: snapshot slots + 1), fixed-interval segments
     bool binomial;
 };
-GradPlan grad_plan(const fd_grid *g, int nt, int nrec, int K, int flags) {
+GradPlan grad_plan(const fd_grid *g, int nt, int nrec, int K, int flags, bool levels) {
     GradPlan p{};
     p.K = K;
     p.binomial = (flags & FD_GRAD_BINOMIAL) != 0;
@@ -1414,10 +1431,10 @@ GradPlan grad_plan(const fd_grid *g, int nt, int nrec, int K, int flags) {
     // two working fields for the resident and binomial schedules (the fixed
     // interval recomputes each segment in its checkpoint's fields)
     p.rot = o;
-    // (with several levels per launch a segment's recompute rotates through
-    // its checkpoint's fields and these two, the resident schedule's forward
-    // pass through the grid's four)
-    if (p.binomial || (g->tb2 ? K < nt : K >= nt)) o += fb * 2;
+    // (levels: with several 2D levels per launch a segment's recompute rotates
+    // through its checkpoint's fields and these two, the resident schedule's
+    // forward pass through the grid's four)
+    if (p.binomial || (levels ? K < nt : K >= nt)) o += fb * 2;
     p.br = o; o += fb * (size_t)p.nbr;
     p.grad = o; o = align_up(o + sizeof(double) * (size_t)g->L.elems, 256);
     p.gpart = o; o = align_up(o + sizeof(float) * (size_t)g->L.elems, 256);
@@ -1433,7 +1450,7 @@ extern "C" int fd_gradient_workspace_bytes(const fd_grid *g, int nt, int nrec, i
     if (!g || !bytes) return fdi_fail(FD_ERR_ARG, "null argument");
     if (nt < 1 || nrec < 1 || K < ((flags & FD_GRAD_BINOMIAL) ? 0 : 1))
         return fdi_fail(FD_ERR_ARG, "nt, nrec >= 1; checkpoint_every >= 1 (>= 0 snapshot slots when binomial)");
-    *bytes = grad_plan(g, nt, nrec, K, flags).total;
+    *bytes = grad_plan(g, nt, nrec, K, flags, g->tb2 > 0).total;
     return FD_OK;
     API_GUARD_END
 }
@@ -1455,7 +1472,12 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     if (!d_obs || !misfit || !grad_m || !workspace || !sh->src_wavelet)
         return fdi_fail(FD_ERR_ARG, "null pointer argument");
     if ((uintptr_t)workspace % 256) return fdi_fail(FD_ERR_ARG, "workspace must be 256-byte aligned");
-    const GradPlan gp = grad_plan(g, nt, sh->nrec, K, flags);
+    bool levels = g->tb2 > 0 && !(flags & FD_GRAD_BINOMIAL);
+    GradPlan gp = grad_plan(g, nt, sh->nrec, K, flags, levels);
+    if (levels && ws_bytes < gp.total) {   // too small for the levels' two fields: one step per launch
+        levels = false;
+        gp = grad_plan(g, nt, sh->nrec, K, flags, levels);
+    }
     if (ws_bytes < gp.total) return fdi_fail(FD_ERR_NOMEM, "gradient workspace %zu < %zu", ws_bytes, gp.total);
     std::vector<fd_ckpt_action> plan;
     if (gp.binomial && (rc = fdi_checkpoint_plan(nt, K, &plan, nullptr))) return rc;
@@ -1552,7 +1574,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     };
     HIPCHK(launch_zero(gacc, gp.rec - gp.grad, s));   // and gpart behind it
 
-    if (g->tb2 && !gp.binomial) {
+    if (levels) {
         // 2D, several levels per launch: the fixed-interval schedule below
         // (the resident one is its case of a single segment)
         const int clast = (gp.nseg - 1) * K;
@@ -1752,7 +1774,7 @@ extern "C" int fd_gradient(fd_grid *g, const fd_shot *sh, int nt, double dt, con
     }
     if (adj_done % kFoldEvery) HIPCHK(launch_fold_f64(L, gacc, gpart, s));
     HIPCHK(launch_field_to_dense_f64(L, gacc, (flags & FD_GRAD_VELOCITY) ? g->vel : nullptr, grad_m, s));
-    if (src_adj && !(g->tb2 && !gp.binomial)) {
+    if (src_adj && !levels) {
         Sample sm = make_sample(g, 0, sh->nsrc, src_adj, adj_smp);
         HIPCHK(launch_sample(sm, LA, g->st, s));
     }

@@ -234,6 +234,8 @@ hipError_t launch_make_pq(const Layout &L, const float *vel, double dt, double b
                           uint16_t *pq, hipStream_t s);
 // `bytes` zero bytes (a multiple of 16) at a 16-byte aligned address.
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
+// The same, and nq groups of 4 elements `apart` bytes apart from `quads` on.
+hipError_t launch_zero_and_quads(void *p, size_t bytes, void *quads, size_t apart, int nq, Store st, hipStream_t s);
 // Zero the pads and halo rows of a 2D float32 field, not its grid quads.
 hipError_t launch_zero_rim2d(const Layout &L, float *f, hipStream_t s);
 hipError_t launch_dense_to_field(const Layout &L, const float *dense, void *f, Store st,

@@ -666,10 +666,14 @@ __global__ __launch_bounds__(kBlock) void k_make_pq(const Layout L, const float 
     }
 }
 
-// 16-byte stores; n float4 groups.
-__global__ __launch_bounds__(kBlock) void k_zero(float4 *f, long long n) {
+// 16-byte stores; n float4 groups.  Then `words` words at each of `nq` places
+// `apart` bytes apart from q on.
+__global__ __launch_bounds__(kBlock) void k_zero(float4 *f, long long n, char *q, size_t apart, int nq, int words) {
     for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
         f[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < nq * words; i += kBlock)
+            reinterpret_cast<uint32_t *>(q + (size_t)(i / words) * apart)[i % words] = 0u;
 }
 
 // Zero the cells of a 2D float32 field that hold no grid quad: the pads left
@@ -943,8 +947,13 @@ hipError_t launch_make_pq(const Layout &L, const float *vel, double dt, double b
 }
 
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s) {
+    return launch_zero_and_quads(p, bytes, nullptr, 0, 0, Store::F32, s);
+}
+
+hipError_t launch_zero_and_quads(void *p, size_t bytes, void *quads, size_t apart, int nq, Store st, hipStream_t s) {
     const long long n = (long long)(bytes / sizeof(float4));
-    hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kBlock), 0, s, (float4 *)p, n);
+    hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kBlock), 0, s, (float4 *)p, n, (char *)quads, apart, nq,
+                       st == Store::F32 ? 4 : 2);
     return hipGetLastError();
 }
 
