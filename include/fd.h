@@ -151,7 +151,8 @@ typedef struct fd_grid_desc {
                               wavefield buffers and 2 (levels - 2) scratch ones, of at
                               most 2 GiB together, in the workspace; results are bitwise
                               those of 1, and a workspace of the size that 1 needs is
-                              accepted and selects it); anything
+                              accepted and selects it; in 2D the count that fd_grid_info
+                              reports means the same as 0); anything
                               else, or 2 where it is not available, is FD_ERR_ARG.
                               Served 2D shots run one step per launch */
     int param_storage;     /* fd_param_storage; FD_PARAM_Q16 in 3D only */

@@ -94,6 +94,9 @@ void fdi_second_derivative_weights(int r, double *c) {
 }
 
 // ----------------------------------------------------------- grid plumbing
+namespace {
+int tb2_auto(const fd_grid_desc *d, const Layout &L);
+}
 bool fdi_check_desc(const fd_grid_desc *d) {
     if (!d) return fdi_fail(FD_ERR_ARG, "null descriptor"), false;
     if (d->ndim != 2 && d->ndim != 3) return fdi_fail(FD_ERR_ARG, "ndim must be 2 or 3"), false;
@@ -116,12 +119,13 @@ bool fdi_check_desc(const fd_grid_desc *d) {
     if (d->sinc_radius < 0 || d->sinc_radius > kMaxSincR)
         return fdi_fail(FD_ERR_ARG, "sinc_radius must be 0..%d", kMaxSincR), false;
     if (!std::isfinite(d->sinc_beta)) return fdi_fail(FD_ERR_ARG, "sinc_beta"), false;
-    if (d->time_block < 0 || d->time_block > 2) return fdi_fail(FD_ERR_ARG, "time_block must be 0, 1 or 2"), false;
+    if (d->time_block < 0 || (d->ndim == 3 && d->time_block > 2))
+        return fdi_fail(FD_ERR_ARG, "time_block must be 0, 1 or 2"), false;
     if (d->param_storage != FD_PARAM_F32 && d->param_storage != FD_PARAM_Q16)
         return fdi_fail(FD_ERR_ARG, "param_storage must be FD_PARAM_F32 or FD_PARAM_Q16"), false;
     if (d->param_storage == FD_PARAM_Q16 && d->ndim != 3)
         return fdi_fail(FD_ERR_ARG, "the 16-bit p code is 3D only"), false;
-    if (d->time_block == 2 && !(d->ndim == 3 && d->storage == FD_STORE_F32 && d->space_order <= 2 * kT2MaxR &&
+    if (d->ndim == 3 && d->time_block == 2 && !(d->storage == FD_STORE_F32 && d->space_order <= 2 * kT2MaxR &&
                                 d->param_storage == FD_PARAM_F32))
         return fdi_fail(FD_ERR_ARG, "time_block 2 needs a 3D float32 grid of space order <= %d with float32 p",
                         2 * kT2MaxR),
@@ -129,6 +133,9 @@ bool fdi_check_desc(const fd_grid_desc *d) {
     long long pts = 1;
     for (int a = 0; a < d->ndim; ++a) pts *= (long long)d->shape[a] + 2LL * d->nbl;
     if (pts > (1LL << 34)) return fdi_fail(FD_ERR_ARG, "grid too large"), false;
+    // 2D: the levels that fd_grid_get_info reports are a valid description of that grid
+    if (d->ndim == 2 && d->time_block > 1 && d->time_block != tb2_auto(d, fdi_layout(d)))
+        return fdi_fail(FD_ERR_ARG, "2D time_block must be 0, 1 or the grid's own level count"), false;
     return true;
 }
 
@@ -244,13 +251,15 @@ inline int tb2_scratch(int levels) { return levels > 2 ? 2 * (levels - 2) : 0; }
 // is bounded by fewer levels (a 432 MB field at so 2, 12000 x 9000: four
 // levels instead of eight, 124 us per step; one step per launch 316).
 constexpr size_t kTb2MaxField = size_t(1) << 30, kTb2MaxScratch = size_t(2) << 30;
-int tb2_levels(const fd_grid_desc *d, const Layout &L) {
-    if (d->ndim != 2 || d->time_block != 0) return 0;
+int tb2_auto(const fd_grid_desc *d, const Layout &L) {
     const size_t field = (size_t)L.elems * (d->storage == FD_STORE_F32 ? 4 : 2);
     if (field > kTb2MaxField) return 0;
     int lev = step2d_levels(L);
     while (field * tb2_scratch(lev) > kTb2MaxScratch) --lev;
     return lev;
+}
+int tb2_levels(const fd_grid_desc *d, const Layout &L) {
+    return d->ndim != 2 || d->time_block == 1 ? 0 : tb2_auto(d, L);
 }
 
 // 16-bit value-and-difference storage, and the element type of a storage.

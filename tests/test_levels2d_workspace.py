@@ -79,3 +79,36 @@ def test_one_step_workspace_is_accepted(grid, gradient):
     assert levels > 1 and had == (1 if grid else levels)
     for i, (a, b) in enumerate(zip(got, want)):
         assert torch.isfinite(b).all() and torch.equal(a, b), i
+
+
+def _accepted(shape, so, storage=0):
+    ok = []
+    for tb in range(0, 10):
+        try:
+            ok.append((tb, _bytes(shape, so, tb, storage)))
+        except _lib.FDError:
+            pass
+    return ok
+
+
+@pytest.mark.parametrize("so", [2, 4, 8, 10, 16])
+@pytest.mark.parametrize("storage", [0, 2])
+def test_only_the_automatic_level_count_is_accepted(so, storage):
+    (a, auto), (b, one), (levels, same) = _accepted((150, 90), so, storage)
+    assert (a, b) == (0, 1) and 2 <= levels <= 16 // (so // 2) and same == auto > one
+
+
+def test_no_level_count_where_there_are_none():
+    assert [tb for tb, _ in _accepted((2481, 1281), 16)] == [0, 1]
+
+
+@pytest.mark.gpu
+def test_reported_level_count_describes_the_grid():
+    need_gpu()
+    from paper_1906_10811_amd import Grid
+    v = torch.full((90, 150), 2000.0, device="cuda")
+    g = Grid((150, 90), (10.0, 10.0), v, space_order=4)
+    h = Grid((150, 90), (10.0, 10.0), v, space_order=4, time_block=g.time_block)
+    assert h.time_block == g.time_block > 1
+    g.close()
+    h.close()
