@@ -252,9 +252,10 @@ inline int tb2_scratch(int levels) { return levels > 2 ? 2 * (levels - 2) : 0; }
 // levels instead of eight, 124 us per step; one step per launch 316).
 constexpr size_t kTb2MaxField = size_t(1) << 30, kTb2MaxScratch = size_t(2) << 30;
 int tb2_auto(const fd_grid_desc *d, const Layout &L) {
-    const size_t field = (size_t)L.elems * (d->storage == FD_STORE_F32 ? 4 : 2);
+    const bool f32 = d->storage == FD_STORE_F32;
+    const size_t field = (size_t)L.elems * (f32 ? 4 : 2);
     if (field > kTb2MaxField) return 0;
-    int lev = step2d_levels(L);
+    int lev = step2d_levels(L, f32);
     while (field * tb2_scratch(lev) > kTb2MaxScratch) --lev;
     return lev;
 }

@@ -203,7 +203,7 @@ struct Step2Args {
     const float *br_in[kTb2MaxLev];
     float *gpart;
 };
-int step2d_levels(const Layout &L);   // levels per launch of a 2D grid, 0: k_step2d
+int step2d_levels(const Layout &L, bool f32);   // levels per launch of a 2D grid, 0: k_step2d
 int sample_rows_blocks(int npts, int lpp);   // workgroups per row of launch_sample_rows
 hipError_t launch_step2d_tb(Step2Args a, Store st, int mode, hipStream_t s);
 hipError_t launch_sample_rows(const SampleRows &smp, Store st, hipStream_t s);

@@ -415,8 +415,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 // Grid axes (x, z); tile 64 x 64 staged whole in LDS with an r halo; each
 // lane computes 4 x points in each of 4 rows.  One step per launch, where the
 // several-level kernel (fd_step2d.hip) is not taken: time_block 1, served
-// shots, fields above 1 GiB, the binomial gradient schedule, and large grids
-// at radius 7 and 8.
+// shots, fields above 1 GiB, the binomial gradient schedule, and grids on
+// which the levels' recomputed ring costs more than they save (step2d_levels).
 template <int R, Store S, int MODE>
 __global__ __launch_bounds__(kBlock) void k_step2d(const StepArgs a) {
     using E = Elem<S>;

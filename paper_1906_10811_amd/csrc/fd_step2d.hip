@@ -334,20 +334,47 @@ void tiles2d(const Layout &L, int nlev, int *ntx, int *ntz) {
 
 // Few tiles: a launch is a fixed latency of about 4 us plus 0.9 us per level
 // while every tile has a CU (nearly) to itself, so as many levels as the halo
-// allows.  Many tiles: the recomputed ring costs what it adds.  Measured per
-// step by level count (float32, us): 181^2 so 4 at 2 / 4 / 8 levels 3.23 /
-// 2.05 / 1.47; 1000 x 600 (608 tiles at 8) 3.41 / 2.35 / 2.01; 2481 x 1281 so 2
-// 6.66 / 4.26 / 3.20, so 4 at 3 / 4 / 5 / 8 6.03 / 5.10 / 5.38 / 6.27; 4081 x
-// 2081 so 6 at 2 / 3 / 4 / 5 18.6 / 17.5 / 17.3 / 21.9, so 8 at 2 / 3 / 4 18.8 /
-// 19.3 / 23.4, so 12 at 2 29.3 (one step per launch 28.5; 2481 x 1281 13.4
-// against 13.9), so 16 at 2 57.9 against 34.3.
-int step2d_levels(const Layout &L) {
+// allows: 181^2 so 4 at 2 / 4 / 8 levels 3.23 / 2.05 / 1.47 us per step, 1000 x
+// 600 (608 tiles at 8) 3.41 / 2.35 / 2.01.
+//
+// Many tiles: the recomputed ring costs what it adds, so the count is that of
+// the lowest time per step by radius, and none (0: one step per launch,
+// k_step2d) where an estimate puts it above one step per launch.  The levels
+// are bound by their arithmetic and take base + slope x (M points that whole
+// tiles cover), 10 % more where the fields exceed the memory-side cache, in any
+// storage; one step is bound by its traffic, base + slope x (M points, rows
+// rounded up to 64), and moves 10 bytes per point instead of 16 in 16-bit
+// storage.  Fitted to float32 and bfloat16 at every order and level count on
+// 0.24 to 108 M points and on grids 5, 20, 60 and 130 points thick; on none of
+// these 272 the choice is more than 1.5 % above one step per launch.  Measured
+// per step (us, levels / one step): 2481 x 1281 so 8 float32 9.5 / 14.4, so 12
+// 14.1 / 15.2, bfloat16 14.0 / 12.4; 4081 x 2081 so 10 float32 26.8 / 29.3,
+// bfloat16 26.9 / 24.5, so 12 30.2 / 29.6 and 30.4 / 23.8; 7000 x 5000 so 6
+// float32 71 / 89, bfloat16 72 / 65; 400000 x 5 so 4 18.6 / 16.4, so 12 50 / 28;
+// so 16 at 2481 x 1281 27.7 / 15.8.  At so 8 in float32 three levels beat two
+// from 10 M points on: 5600 x 3000 42.2, 48.7, one step 47.2; 7000 x 5000 87.4,
+// 99.3, 92.5.
+int step2d_levels(const Layout &L, bool f32) {
     constexpr int kFewTiles = 700;
-    constexpr int many[kMaxR + 1] = {0, 8, 4, 4, 2, 2, 2, 0, 0};   // (0: one step per launch, k_step2d)
+    constexpr int many[kMaxR + 1] = {0, 8, 4, 4, 2, 2, 2, 0, 0};
+    constexpr double base[] = {0, 0, 1.5, 1.5, 1.5, 2.0, 2.0}, slope[] = {0, 0, 1.13, 1.95, 2.05, 2.9, 3.4};
+    constexpr double kCacheBytes = 256.0 * 1024 * 1024;
     const int most = std::min(kTb2MaxLev, kTb2Halo / L.r);
     int ntx, ntz;
     tiles2d(L, most, &ntx, &ntz);
-    return (long long)ntx * ntz <= kFewTiles ? most : many[L.r];
+    if ((long long)ntx * ntz <= kFewTiles) return most;
+    const double n = 1e-6 * L.nx * L.nz;
+    const int lev = L.r == 4 && f32 && n > 10 ? 3 : many[L.r];
+    if (lev == 0 || L.r == 1) return lev;   // (at radius 1 eight levels win everywhere)
+    tiles2d(L, lev, &ntx, &ntz);
+    const int H = L.r * lev, Hx = (H + 3) & ~3;
+    const double covered = 1e-6 * ntx * (4 * kW4 - 2 * Hx) * ntz * (kRows - 2 * H);
+    const double rows = 1e-6 * ((L.nx + kTileX - 1) / kTileX * kTileX) * L.nz;
+    const bool spills = 1e6 * n * (f32 ? 20 : 12) > kCacheBytes;
+    const double levels_us = (base[L.r] + slope[L.r] * covered) * (spills ? 1.1 : 1.0);
+    const double one_us = f32 ? (L.r <= 4 ? 5.5 + 2.5 * rows : 6.0 + 2.65 * rows)
+                              : (L.r <= 4 ? 5.0 + 1.9 * rows : L.r == 5 ? 5.5 + 2.2 * rows : 4.5 + 2.2 * rows);
+    return levels_us <= one_us ? lev : 0;
 }
 
 int sample_rows_blocks(int npts, int lpp) { return (npts + kNT / lpp - 1) / (kNT / lpp); }
