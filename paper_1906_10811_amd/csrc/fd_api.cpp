@@ -746,14 +746,19 @@ StepArgs base_args(const fd_grid *g) {
     // and 7 % at 280^3 (the written lines crowd out of L2 the neighbour rows
     // that the halo loads expect there).
     a.out_cached = (g->st != Store::F32 && g->wp.field_bytes <= kCachedField) ? 1 : 0;
-    // Float32 p of up to kCachedField bytes is read with ordinary loads, so
-    // that what of it the memory-side cache keeps from the step before is not
-    // fetched again.  Measured at so 8 (us per step, non-temporal -> ordinary):
-    // float32 224^3 33.7 -> 31.6, 272^3 59.5 -> 55.6, 320^3 (131 MB of p) 80.8
-    // -> 77.5, 336^3 101.4 -> 100.9, 416^3 191 -> 198; bfloat16 272^3 43.4 ->
-    // 41.0, 336^3 72.8 -> 73.8, 416^3 130 -> 135.  Codes of p show no
-    // difference at any size and stay non-temporal.
-    a.p_cached = (size_t)L.nx * L.ny * L.nz * sizeof(float) <= kCachedField;
+    // Float32 p that fits the memory-side cache beside the fields is read with
+    // ordinary loads, so that what of it that cache keeps from the step before
+    // is not fetched again.  Measured (us per step, non-temporal -> ordinary):
+    // float32 so 8 224^3 33.7 -> 31.6, 272^3 59.5 -> 55.6, 320^3 (131 MB of p)
+    // 80.8 -> 77.5, 336^3 101.4 -> 100.9, 416^3 191 -> 198; bfloat16 so 4 250^3
+    // 36.1 -> 29.9, 300^3 53.9 -> 45.1, 320^3 59.6 -> 57.9, 416^3 130 -> 135.  The
+    // difference form keeps a third field: so 4 250^3 46.8 -> 38.5, 272^3 (80 MB)
+    // 53.8 -> 51.7, 450 x 330 x 150 (89 MB) 58.4 -> 64.3, 320^3 68.6 -> 74.8; at so
+    // 14 and 16 its arithmetic is longer and it gains up to 320^3 (450 x 330 x 150
+    // so 14 86.9 -> 84.4).  Codes of p show no difference at any size and stay
+    // non-temporal.
+    const size_t p_bytes = (size_t)L.nx * L.ny * L.nz * sizeof(float);
+    a.p_cached = p_bytes <= (g->diff && L.r <= 6 ? kCachedPDiff : kCachedField);
     a.ntz = g->ntz[kPlain];
     a.zchunk = g->zchunk[kPlain];
     return a;

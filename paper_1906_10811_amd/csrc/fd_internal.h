@@ -19,7 +19,9 @@ constexpr int kMaxChunk = 512;    // z planes per 3D workgroup at most
 // rather than non-temporal ones (16-bit 3D fields, 2D diffusion fields), and
 // largest float32 p a 3D step reads with ordinary loads: a field this small
 // can still sit in the 256 MB memory-side cache when the next step reads it.
+// kCachedPDiff: the same for p beside the three fields of the difference form.
 constexpr size_t kCachedField = size_t(128) << 20;
+constexpr size_t kCachedPDiff = size_t(80) << 20;
 // Bytes of the static device scratch behind fd_diffusion_run_noalloc (two
 // pitched float32 fields: a 2500 x 2500 grid at every space order).
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
@@ -114,6 +116,11 @@ struct Imaging {
 // (kImage3: 3D only)
 enum StepMode { kPlain = 0, kBracket = 1, kImage = 2, kDiff = 3, kImage3 = 4 };
 constexpr int kStepModes = 5;
+
+// Form of p in a 3D step kernel: float32, 16-bit codes, or float32 in a kernel
+// that reads it with ordinary loads (where the storage has kernels of its own
+// for that; elsewhere kPFloat's take either kind of load by p_cached).
+enum PForm { kPFloat = 0, kPCodes = 1, kPCached = 2 };
 
 struct StepArgs {
     Layout L;

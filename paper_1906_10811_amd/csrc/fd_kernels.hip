@@ -827,16 +827,17 @@ using Tab2 = Table2<S, MODE, 1, 2, 3, 4, 5, 6, 7, 8>;
 // The gradient modes exist for float32 storage and p only, the difference
 // storage for 16-bit 3D fields only, the 16-bit p codes in 3D only (kPlain
 // and kDiff); the 3D kernels come from the storage type's own unit.
-StepFn pick_step(int ndim, int r, Store st, int mode, int tw4, bool pq) {
+StepFn pick_step(int ndim, int r, Store st, int mode, int tw4, int pf) {
+    const bool pq = pf == kPCodes;
     if (ndim == 3) {
         if (pq && mode != kPlain && mode != kDiff) return nullptr;
         if ((mode == kBracket || mode == kImage || mode == kImage3) && st != Store::F32) return nullptr;
         if (mode == kDiff && st == Store::F32) return nullptr;
         switch (st) {
-            case Store::F32: return step3d_kernel_f32(r, mode, tw4, pq);
-            case Store::F16: return mode == kDiff ? step3d_kernel_f16_diff(r, tw4, pq) : step3d_kernel_f16(r, tw4, pq);
+            case Store::F32: return step3d_kernel_f32(r, mode, tw4, pf);
+            case Store::F16: return mode == kDiff ? step3d_kernel_f16_diff(r, tw4, pf) : step3d_kernel_f16(r, tw4, pf);
             case Store::BF16:
-                return mode == kDiff ? step3d_kernel_bf16_diff(r, tw4, pq) : step3d_kernel_bf16(r, tw4, pq);
+                return mode == kDiff ? step3d_kernel_bf16_diff(r, tw4, pf) : step3d_kernel_bf16(r, tw4, pf);
         }
         return nullptr;
     }
@@ -889,7 +890,8 @@ int step_t2_blocks_per_cu(int r) {
 }
 
 hipError_t launch_step(const StepArgs &a, Store st, int mode, hipStream_t s) {
-    StepFn f = pick_step(a.L.ndim, a.L.r, st, mode, a.shape3, a.pq != nullptr);
+    const int pf = a.pq ? kPCodes : a.p_cached ? kPCached : kPFloat;
+    StepFn f = pick_step(a.L.ndim, a.L.r, st, mode, a.shape3, pf);
     if (!f) return hipErrorInvalidValue;
     const int tiles = (a.ntx * a.nty + (a.L.ndim == 3 ? a.nstrip : 0)) * a.ntz;
     const int blocks = tiles + a.nsamp_blocks;
@@ -899,7 +901,7 @@ hipError_t launch_step(const StepArgs &a, Store st, int mode, hipStream_t s) {
 }
 
 int step_blocks_per_cu(int ndim, int r, Store st, int mode, int tw4, bool pq) {
-    StepFn f = pick_step(ndim, r, st, mode, tw4, pq);
+    StepFn f = pick_step(ndim, r, st, mode, tw4, pq ? kPCodes : kPFloat);
     if (!f) return 0;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(f), kBlock, 0) !=

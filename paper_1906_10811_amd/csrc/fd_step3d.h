@@ -28,11 +28,11 @@ using StepFn = void (*)(const StepArgs);
 // storage form: two levels or value plus difference) for radius r, step
 // mode, tile shape code (16, 8 or kShapeMixed = 0) and p in float32 or as
 // 16-bit codes; null where that combination is not built.
-StepFn step3d_kernel_f32(int r, int mode, int shape, bool pq);
-StepFn step3d_kernel_f16(int r, int shape, bool pq);
-StepFn step3d_kernel_f16_diff(int r, int shape, bool pq);
-StepFn step3d_kernel_bf16(int r, int shape, bool pq);
-StepFn step3d_kernel_bf16_diff(int r, int shape, bool pq);
+StepFn step3d_kernel_f32(int r, int mode, int shape, int pf);
+StepFn step3d_kernel_f16(int r, int shape, int pf);
+StepFn step3d_kernel_f16_diff(int r, int shape, int pf);
+StepFn step3d_kernel_bf16(int r, int shape, int pf);
+StepFn step3d_kernel_bf16_diff(int r, int shape, int pf);
 
 namespace {
 
@@ -346,11 +346,25 @@ struct Smem3 {
     static constexpr int kSize = kPp + (kMaxChunk + 1 + 3) / 4;
 };
 
+// Whether float32 p has kernels of its own for ordinary loads (kPCached).  The
+// choice at run time in the plane loop splits it into blocks that the compiler
+// schedules apart.  In 16-bit storage at these radii that cost 2-5 % where p is
+// not cached and most of what caching gains where it is; us per step, choice
+// in the loop -> kernels of their own: bfloat16 336^3 so 10 88.7 -> 86.4, so 12
+// 104.4 -> 101.0, 320^3 so 10 79.1 -> 75.9; F16 difference 336^3 so 12 114.5 ->
+// 111.4, 450 x 330 x 150 so 10 70.3 -> 65.6.  The difference form at so 14 and 16
+// is 1-6 % faster with the choice in the loop (250^3 so 16 59.1, 62.3), the
+// others do not differ.
+template <int R, Store S, int MODE>
+constexpr bool kSplitP = S != Store::F32 && R >= 5 && (MODE == kPlain || (MODE == kDiff && R <= 6));
+
 // One workgroup's step: the xy tile at (x0, y0) of TW float4 columns per
 // row (16: 64 x 16 points, 8: 32 x 32) and z chunk bz; tid is the tile's
-// row in the source plane-pointer table.
-template <int R, Store S, int MODE, int TW, bool PQ>
+// row in the source plane-pointer table.  MIXED: the kernel holds both tile
+// shapes.
+template <int R, Store S, int MODE, int TW, int PF, bool MIXED>
 __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int x0, int y0, int bz, int tid) {
+    constexpr bool PQ = PF == kPCodes;
     static_assert(!PQ || MODE == kPlain || MODE == kDiff, "the gradient modes read float32 p");
     using E = Elem<S>;
     using T = typename E::T;
@@ -509,7 +523,7 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
         for (int k = 0; k < HPT; ++k) r.hv[k] = E::ld4raw(U + hoff[k] + fo);
         if constexpr (PQ)
             r.pv = ld2nt_u32(Pq + base + zo);
-        else if (a.p_cached)
+        else if (kSplitP<R, S, MODE> ? PF == kPCached : a.p_cached)
             r.pv = *reinterpret_cast<const float4 *>(Pp + base + zo);
         else
             r.pv = ld4nt_f32(Pp + base + zo);
@@ -694,12 +708,19 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
         body(I, st + i, set(I), set(std::integral_constant<int, i + 2>{}));
         return st + i + 1 < len;
     };
-    if constexpr (kRot && (R == 5 || R == 8)) {
-        // One copy of the long group, left at the chunk's last plane.  With a
-        // second copy for the remaining planes the compiler kept the arrays of
-        // the difference form at radius 8 in scratch memory (336^3 so 16 349 us
-        // per step, 127 now), and the other 16-bit forms at radius 5 and 8 were
-        // up to 9 % slower; at radius 6 and 7 the second copy is 1-3 % faster.
+    // One copy of the long group, left at the chunk's last plane, instead of a
+    // second copy for the remaining planes.  With two copies the compiler keeps
+    // arrays of these kernels in scratch memory (about 500 bytes per lane): of
+    // both tile shapes together at radius 5 and 6 and of the difference form on
+    // 64 x 16 tiles at radius 8, all reached by tile_x only.  336^3 F16
+    // difference so 16 on 64 x 16 tiles 354 us per step with two copies, 126 with
+    // one; 280^3 F16 so 12 on mixed tiles 138 and 65.  At radius 5 and 8 one copy
+    // is also 1-3 % faster on small grids, whose p is cached (160^3 so 10 bfloat16
+    // 18.7 -> 18.4, 250^3 so 16 51.0 -> 49.6), and in the difference form and
+    // bfloat16 at radius 8; else, and at the other radii, two are 1-3 % faster.
+    if constexpr (kRot && (MIXED ? R >= 5
+                                 : (R == 5 && PF == kPCached) ||
+                                       (R == 8 && (MODE == kDiff || S == Store::BF16 || PF == kPCached)))) {
         while (all_of_seq(std::make_integer_sequence<int, UNR>{}, plane_step)) st += UNR;
     } else {
         for (; st + UNR <= len; st += UNR) static_for<0, UNR>(plane_step);
@@ -713,9 +734,9 @@ __device__ __forceinline__ void step3d_tile(const StepArgs &a, float4 *smem, int
 // SHAPE 0: 64 x 16 tiles over the ntx whole 64-point columns and, beside
 // them, nstrip 32 x 32 tiles for the last, narrower x column (at most 32
 // points), which a 64-point tile would fill to half or less.  Tiles are
-// numbered x fastest, then y, then the strip, then z chunk.  PQ: p is read
-// as 16-bit codes (a.pq) instead of float32.
-template <int R, Store S, int MODE, int SHAPE, bool PQ>
+// numbered x fastest, then y, then the strip, then z chunk.  PF: the form of p
+// (kPCodes: 16-bit codes, a.pq).
+template <int R, Store S, int MODE, int SHAPE, int PF>
 __global__ __launch_bounds__(kBlock) void k_step3d(const StepArgs a) {
     constexpr int kSmem = SHAPE == 16 ? Smem3<R, 16>::kSize
                           : SHAPE == 8 ? Smem3<R, 8>::kSize
@@ -736,11 +757,11 @@ __global__ __launch_bounds__(kBlock) void k_step3d(const StepArgs a) {
     const int u = t % tiles, bz = t / tiles;
     if constexpr (SHAPE == 0) {
         if (u < nmain)
-            step3d_tile<R, S, MODE, 16, PQ>(a, smem, (u % a.ntx) * 64, (u / a.ntx) * 16, bz, u);
+            step3d_tile<R, S, MODE, 16, PF, true>(a, smem, (u % a.ntx) * 64, (u / a.ntx) * 16, bz, u);
         else
-            step3d_tile<R, S, MODE, 8, PQ>(a, smem, a.ntx * 64, (u - nmain) * 32, bz, u);
+            step3d_tile<R, S, MODE, 8, PF, true>(a, smem, a.ntx * 64, (u - nmain) * 32, bz, u);
     } else {
-        step3d_tile<R, S, MODE, SHAPE, PQ>(a, smem, (u % a.ntx) * 4 * SHAPE, (u / a.ntx) * (kBlock / SHAPE), bz,
+        step3d_tile<R, S, MODE, SHAPE, PF, false>(a, smem, (u % a.ntx) * 4 * SHAPE, (u / a.ntx) * (kBlock / SHAPE), bz,
                                            u);
     }
 }
@@ -748,25 +769,33 @@ __global__ __launch_bounds__(kBlock) void k_step3d(const StepArgs a) {
 // Kernel lookup of one storage type and step mode over the radii Rs.
 template <Store S, int MODE, int... Rs>
 struct Step3dTable {
-    template <bool PQ>
+    template <int PF>
     static StepFn get(int r, int shape) {
         StepFn f = nullptr;
-        if (shape == 16) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 16, PQ>, 0) : 0), ...);
-        if (shape == 8) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 8, PQ>, 0) : 0), ...);
+        if (shape == 16) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 16, form<Rs, 16>(PF)>, 0) : 0), ...);
+        if (shape == 8) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 8, form<Rs, 8>(PF)>, 0) : 0), ...);
         // (radii 7 and 8 always run 32 x 32 tiles: no mixed kernel)
-        if (shape == 0) ((r == Rs ? (f = k_step3d<Rs, S, MODE, (Rs <= 6 ? 0 : 8), PQ>, 0) : 0), ...);
+        if (shape == 0) ((r == Rs ? (f = k_step3d<Rs, S, MODE, (Rs <= 6 ? 0 : 8), form<Rs, 0>(PF)>, 0) : 0), ...);
         return f;
+    }
+    // kPCached only where it has kernels (at radius 7 and 8 not for 64 x 16
+    // tiles, which the automatic choice never takes there)
+    template <int R, int SHAPE>
+    static constexpr int form(int pf) {
+        const bool split = kSplitP<R, S, MODE> && (SHAPE != 16 || R <= 6);
+        return pf == kPCached && !split ? kPFloat : pf;
     }
 };
 
 // (p codes: kPlain and kDiff only)
 template <Store S, int MODE>
-StepFn step3d_get(int r, int shape, bool pq) {
+StepFn step3d_get(int r, int shape, int pf) {
     using Tb = Step3dTable<S, MODE, 1, 2, 3, 4, 5, 6, 7, 8>;
-    if constexpr (MODE == kPlain || MODE == kDiff)
-        return pq ? Tb::template get<true>(r, shape) : Tb::template get<false>(r, shape);
-    else
-        return pq ? nullptr : Tb::template get<false>(r, shape);
+    if (pf == kPCodes) {
+        if constexpr (MODE == kPlain || MODE == kDiff) return Tb::template get<kPCodes>(r, shape);
+        return nullptr;
+    }
+    return pf == kPCached ? Tb::template get<kPCached>(r, shape) : Tb::template get<kPFloat>(r, shape);
 }
 
 }  // namespace
