@@ -1,5 +1,5 @@
 // fd_diffuse2d.hip -- the thesis's benchmark operator (Section 5.1.2): forward
-// Euler steps of u_t = nu Lap u in 2D, several levels per launch, by two
+// Euler steps of u_t = nu Lap u in 2D, several levels per launch, by three
 // kernels with the same arithmetic (their fields are bitwise equal).
 //
 // k_diffuse2d_strip, for grids that fill the GPU with strips: one step reads
@@ -12,9 +12,15 @@
 // is no LDS, no barrier and no staging.  Recomputed are R T points at either
 // end of a strip (rounded to 4) and R T rows at either end of a chunk.
 //
-// k_diffuse2d_tile, for small grids, where latency is the bound: the scheme of
-// the 2D acoustic levels (fd_step2d.hip), a 64 x 64 region staged once and
-// advanced in registers with the neighbours' level in LDS.
+// k_diffuse2d_tile, for small and narrow grids, where latency or the lanes of
+// a strip are the bound: the scheme of the 2D acoustic levels (fd_step2d.hip),
+// a 64 x 64 region staged once and advanced in registers with the neighbours'
+// level in LDS.
+//
+// k_diffuse2d_one, a single level of whole 64 x 64 tiles, where a launch takes
+// one level and a strip's halo costs more than it saves: so 16 up to 20 M
+// points, single steps of fields beyond the memory-side cache's reach, narrow
+// grids at high order.
 #include "fd_step3d.h"
 
 #include <algorithm>
@@ -365,10 +371,12 @@ DiffFn one_kernel(int r, bool cached) {
 //   2500^2                       3.28 / 3.75   4.95 / 5.71   8.27 / 8.65   14.1 / 11.4   (7.3 8.4 12.4 15.7)
 //   10000^2                      46.4 / 33.6   74.3 / 52.0   128 / 84.8    213 / 110     (85 97 143 174)
 // The strips win once they fill the GPU: above 7 M points up to radius 4, 4 M
-// at radius 5 and 6, 2 M beyond; single levels at radius 1 and 2 above 4 M.
+// at radius 5 and 6, 2 M beyond (where radius 8 takes single levels up to 20 M,
+// see use_one); single levels above 4 M up to radius 3, 6.5 M at radius 4
+// (2500^2 tiles 13.2, strips 13.4; 2600^2 14.7, 13.9).
 bool use_tiles(const Layout &L, int most) {
     const long long n = (long long)L.nx * L.nz;
-    if (most == 1 && L.r <= 2) return n <= 4000000;
+    if (most == 1 && L.r <= 4) return n <= (L.r <= 3 ? 4000000 : 6500000);
     return n <= (L.r <= 4 ? 7000000 : L.r <= 6 ? 4000000 : 2000000);
 }
 
@@ -416,23 +424,40 @@ int strip_levels(const Layout &L, int most, bool cached) {
     return 1;
 }
 
-// One level per launch (asked for, or the last of a count).  Measured (us):
+// One level per launch (asked for, the last of a count, or the choice at radius
+// 8).  Measured (us):
 //                       so 2          so 4          so 8   so 16
 //   10000^2, strips       176 (162)     177 (163)     172    177     (16384 waves)
 //            this kernel  150           151           158    173
+//   5700^2,  strips       55.7          57.8          --     67.3
+//            this kernel  54.9          55.9          --     68.4
 //   2500^2,  tiles        10.2          10.6          11.6   19.6
 //            strips       -- (9.2)      -- (9.6)      --     15.5
 //            this kernel  10.0          10.4          11.8   15.3
 //   3000^2,  strips       12.5 (12.0)   14.0 (12.3)   15.3   20.4
 //            this kernel  13.4          13.8          15.6   18.8
-// So: fields beyond the memory-side cache's reach take this kernel; others
-// take it where the strips' 2 R recomputed rows weigh (radius 8, up to 20 M
-// points; 5000^2 41.2 by strips, 43.3) and at radius 4 on the
-// largest grids of tiles (2600^2 13.1 against 12.2).
-bool use_one(const Layout &L, bool cached, bool tiles) {
+// So: fields beyond the memory-side cache's reach take this kernel, up to
+// radius 3 from 31 M points on (at radius 4 5700^2 measured 59.7 against 60.9 on
+// one GPU and 50.4 against 47.9 on another), and at radius 8 where the strips' 2 R recomputed rows weigh, up to 20 M points
+// (5000^2 41.2 by strips, 43.3).
+bool use_one(const Layout &L, bool cached) {
     const long long n = (long long)L.nx * L.nz;
-    return !cached || (tiles ? L.r == 4 && n > 6500000 : L.r == 8 && n <= 20000000);
+    return !cached || (L.r <= 3 && n > 31000000) || (L.r == 8 && n <= 20000000);
 }
+
+// Grids that leave many of a strip's lanes outside take the other kernels
+// however many points they have: tiles up to radius 5, single levels of whole
+// tiles beyond (there a tile's two levels stage twice what they write), the
+// last also below the strips' line on grids of less than a third of a strip.
+// Measured (us per step, strips / tiles / single levels): 8 x 1000000 so 2 76 /
+// 27 / 63, so 8 165 / 56, so 16 292 / 129 / 110; 64 x 125000 so 4 16.0 / 9.4; 100
+// x 160000 so 10 37.6 / 32.5, so 12 43.5 / 40.2 / 35.5; 260 x 61538 so 8 25.5 /
+// 21.4, so 12 34.9 / 36.2 / 32.2; 500 x 10000 so 12 13.1 / 12.6 / 12.0; at 300 x
+// 26666 so 14 strips win again, 21.8 / 22.5 / 22.1.  Asked for one level, tiles
+// beyond the memory-side cache's reach (8 x 1000000 so 2 71.6, single levels
+// 62.7) and strips used to less than 0.6 up to radius 4 (300 x 30000 so 8 19.4,
+// 18.0) give way to whole tiles as well.
+double least_lanes(int r) { return r <= 5 ? 0.52 : r == 6 ? 0.66 : r == 7 ? 0.55 : 0.60; }
 
 }  // namespace
 
@@ -449,17 +474,27 @@ hipError_t launch_diffuse2d(const Layout &L, const float *u, float *out, float w
         a.wz[j] = wz[j];
     }
     a.out_cached = (size_t)L.elems * sizeof(float) <= kCachedField;
-    const bool tiles = use_tiles(L, most);
-    a.nlev = tiles ? std::min(most, tile_levels(L)) : strip_levels(L, most, a.out_cached);
-    if (a.nlev == 1 && use_one(L, a.out_cached, tiles)) {
+    bool tiles = use_tiles(L, most), one = false;
+    a.nlev = strip_levels(L, most, a.out_cached);
+    strip_shape(L, a.nlev, &a.nstrip, &a.chunk);
+    const double lanes = (double)L.nx / ((double)a.nstrip * kStrip);
+    if (lanes < least_lanes(L.r)) {
+        if (L.r >= 6) one = !tiles || (lanes < 0.3 && (long long)L.nx * L.nz > 2000000);
+        else one = most == 1 && !a.out_cached;
+        tiles = !one;
+    } else if (!tiles) {
+        one = a.nlev == 1 && (use_one(L, a.out_cached) || (L.r <= 4 && lanes < 0.6));
+    }
+    if (one) {
+        a.nlev = 1;
         a.nstrip = (L.nx + kTileX - 1) / kTileX;
         hipLaunchKernelGGL(one_kernel(L.r, a.out_cached), dim3(a.nstrip * ((L.nz + kTile2Z - 1) / kTile2Z)), dim3(kBlock), 0, s, a);
     } else if (tiles) {
         int ntz;
+        a.nlev = std::min(most, tile_levels(L));
         tile_shape(L, a.nlev, &a.nstrip, &ntz);
         hipLaunchKernelGGL(tile_kernel(L.r), dim3(a.nstrip * ntz), dim3(kNT), 0, s, a);
     } else {
-        strip_shape(L, a.nlev, &a.nstrip, &a.chunk);
         hipLaunchKernelGGL(strip_kernel(L.r, a.nlev), dim3(a.nstrip * ((L.nz + a.chunk - 1) / a.chunk)), dim3(64), 0,
                            s, a);
     }

@@ -1,6 +1,7 @@
 // fd_diffusion.cpp -- the thesis's benchmark problem (Section 5.1.2): 2D
 // diffusion, first order in time, on the pitched 2D layout of libfd.  A
-// host time loop enqueues one tiled step kernel per time step, ping-ponging
+// host time loop enqueues launches of one or several time levels each
+// (launch_diffuse2d chooses the kernel and the count), ping-ponging
 // between two workspace fields (the new level cannot overwrite the old one:
 // every point of u^n is read by its neighbours' updates).
 #include <hip/hip_runtime.h>
