@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kW4 = 16, kRows = 64, kK = 2;   // staged float4 columns, rows; rows per lane
 constexpr int kNT = kW4 * kRows / kK;         // lanes of a workgroup
+constexpr int kNodeReach = 15;                // Step2Args::node_reach at most (windowed sinc of half-width 8)
 constexpr int kSrcCap = 128;                  // source points of a tile whose values are formed up front
 
 // u^{n+1} .. at the sampled levels of the previous launch
@@ -113,12 +114,36 @@ __global__ __launch_bounds__(kNT) void k_step2d_tb(const Step2Args a) {
     const int za = max(z0, 0), zb = min(z0 + kRows, L.nz);
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-        e0[i] = 0;
-        if (a.vals && ct0 + i <= ct1) {
-            const int *q = a.inj_pp + (long long)(ct0 + i) * (L.nz + 1);
-            e0[i] = q[za];
-            ns += q[zb] - e0[i];
+        const int *q = a.inj_pp + (long long)min(ct0 + i, ct1) * (L.nz + 1);
+        e0[i] = q[za];
+        nsum[i] = q[zb];
+    }
+    // Whether the tile holds points that are sampled (its intermediate levels
+    // are then stored for the next launch's sampling).  The tables leave out
+    // nodes of weight zero, which are read all the same (0 times what an
+    // earlier run left there may be NaN): every node lies within node_reach of
+    // one that the tables have.  (All pointers are loaded before the first is
+    // waited for, a column again rather than behind a branch.)
+    constexpr int NN = (4 * kW4 + 2 * kNodeReach + kTileX - 2) / kTileX + 1;   // columns in reach, at most
+    int nlo[NN], nhi[NN];
+    const bool sampled = a.node_pp && nlev > 2;
+    if (sampled) {
+        const int n = a.node_reach;
+        const int xu0 = max(x0 + Hx - n, 0), xu1 = min(x0 + 4 * kW4 - Hx + n, L.nx) - 1;
+        const int zu0 = max(z0 + H - n, 0), zu1 = min(z0 + kRows - H + n, L.nz);
+#pragma unroll
+        for (int i = 0; i < NN; ++i) {
+            const int *q = a.node_pp + (long long)min(xu0 / kTileX + i, xu1 / kTileX) * (L.nz + 1);
+            nlo[i] = q[zu0];
+            nhi[i] = q[zu1];
         }
+    }
+    bool nodes = false;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) nodes |= sampled && nlo[i] < nhi[i];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        if (a.vals && ct0 + i <= ct1) ns += nsum[i] - e0[i];
         nsum[i] = ns;
     }
     auto entry = [&](int j) {   // table index of the j-th source point
@@ -155,21 +180,6 @@ __global__ __launch_bounds__(kNT) void k_step2d_tb(const Step2Args a) {
             s_val[t * kSrcCap + j] = src_val(e, t);
         }
 
-    // Whether the tile holds points that are sampled (its intermediate levels
-    // are then stored for the next launch's sampling).  The tables leave out
-    // nodes of weight zero, which are read all the same (0 times what an
-    // earlier run left there may be NaN): every node lies within node_reach of
-    // one that the tables have.
-    bool nodes = false;
-    if (a.node_pp) {
-        const int n = a.node_reach;
-        const int xu0 = max(x0 + Hx - n, 0), xu1 = min(x0 + 4 * kW4 - Hx + n, L.nx) - 1;
-        const int zu0 = max(z0 + H - n, 0), zu1 = min(z0 + kRows - H + n, L.nz);
-        for (int ct = xu0 / kTileX; ct <= xu1 / kTileX; ++ct) {
-            const int *q = a.node_pp + (long long)ct * (L.nz + 1);
-            nodes |= q[zu0] < q[zu1];
-        }
-    }
     // the lane's quads that are this tile's to write
     bool mine[kK];
 #pragma unroll
