@@ -518,7 +518,6 @@ def bench_diffusion(torch, dev, stream):
         u0[n // 4: n // 2, n // 4: n // 2] = 2.0
         res = torch.empty_like(u0)
         for so in (2, 4, 8, 12):
-            r = so // 2
             dt = 0.8 * diffusion_dt_limit((n, n), (h, h), so, 0.5)
             diffusion(u0, (h, h), so, 0.5, dt, 10, out=res, stream=stream, time_block=1)
             torch.cuda.synchronize()
@@ -531,9 +530,7 @@ def bench_diffusion(torch, dev, stream):
             torch.cuda.synchronize()
             secs = e0.elapsed_time(e1) / 1000.0
             gpts = n * n * 1000 / secs / 1e9
-            # the library's automatic choice: several levels per launch (8 B per
-            # point and launch of lev steps)
-            lev = {2500: {1: 8, 2: 4, 4: 2, 6: 2}, 10000: {1: 8, 2: 8, 4: 4, 6: 2}}[n][r]
+            # the library's automatic choice: several levels per launch
             diffusion(u0, (h, h), so, 0.5, dt, 10, out=res, stream=stream, time_block=0)
             torch.cuda.synchronize()
             with torch.cuda.stream(stream):
@@ -545,8 +542,7 @@ def bench_diffusion(torch, dev, stream):
             gpts_tb = n * n * 1000 / secs_tb / 1e9
             out["%d^2 so%d" % (n, so)] = dict(
                 gpts=round(gpts, 1), frac_hbm=round(gpts * 8.0 / HBM_PEAK_GBS, 4),
-                auto_gpts=round(gpts_tb, 1), auto_steps_per_launch=lev,
-                auto_frac_hbm=round(gpts_tb * 8.0 / lev / HBM_PEAK_GBS, 4))
+                auto_gpts=round(gpts_tb, 1))
         del u0, res
     # the FP64 oracle on the host, a few steps of the 2500^2 so-8 case
     import oracle
