@@ -21,10 +21,10 @@ LIB = os.path.join(PKG, "libfd.so")
 ARCH = "gfx950"
 
 # the 3D step's instantiations are spread over units of similar size that
-# compile in parallel
-HIP_SOURCES = ["fd_kernels.hip", "fd_step2d.hip", "fd_diffuse2d.hip",
-               "fd_step3d_f32.hip", "fd_step3d_f16.hip", "fd_step3d_f16_diff.hip",
-               "fd_step3d_bf16.hip", "fd_step3d_bf16_diff.hip"]
+# compile in parallel (the longest first)
+HIP_SOURCES = ["fd_step3d_f16_diff.hip", "fd_step3d_bf16_diff.hip", "fd_step3d_f32.hip",
+               "fd_step3d_f16.hip", "fd_step3d_bf16.hip", "fd_step3d_f16_cached.hip", "fd_step3d_bf16_cached.hip",
+               "fd_diffuse2d.hip", "fd_step2d.hip", "fd_kernels.hip"]
 HOST_SOURCES = ["fd_api.cpp", "fd_serve.cpp", "fd_diffusion.cpp", "fd_checkpoint.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -833,11 +833,15 @@ StepFn pick_step(int ndim, int r, Store st, int mode, int tw4, int pf) {
         if (pq && mode != kPlain && mode != kDiff) return nullptr;
         if ((mode == kBracket || mode == kImage || mode == kImage3) && st != Store::F32) return nullptr;
         if (mode == kDiff && st == Store::F32) return nullptr;
+        if (pf == kPCached && st != Store::F32) {
+            StepFn f = st == Store::F16 ? step3d_kernel_f16_cached(r, mode, tw4) : step3d_kernel_bf16_cached(r, mode, tw4);
+            if (f) return f;
+        }
         switch (st) {
-            case Store::F32: return step3d_kernel_f32(r, mode, tw4, pf);
-            case Store::F16: return mode == kDiff ? step3d_kernel_f16_diff(r, tw4, pf) : step3d_kernel_f16(r, tw4, pf);
+            case Store::F32: return step3d_kernel_f32(r, mode, tw4, pq);
+            case Store::F16: return mode == kDiff ? step3d_kernel_f16_diff(r, tw4, pq) : step3d_kernel_f16(r, tw4, pq);
             case Store::BF16:
-                return mode == kDiff ? step3d_kernel_bf16_diff(r, tw4, pf) : step3d_kernel_bf16(r, tw4, pf);
+                return mode == kDiff ? step3d_kernel_bf16_diff(r, tw4, pq) : step3d_kernel_bf16(r, tw4, pq);
         }
         return nullptr;
     }

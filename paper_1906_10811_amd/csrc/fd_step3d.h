@@ -28,11 +28,13 @@ using StepFn = void (*)(const StepArgs);
 // storage form: two levels or value plus difference) for radius r, step
 // mode, tile shape code (16, 8 or kShapeMixed = 0) and p in float32 or as
 // 16-bit codes; null where that combination is not built.
-StepFn step3d_kernel_f32(int r, int mode, int shape, int pf);
-StepFn step3d_kernel_f16(int r, int shape, int pf);
-StepFn step3d_kernel_f16_diff(int r, int shape, int pf);
-StepFn step3d_kernel_bf16(int r, int shape, int pf);
-StepFn step3d_kernel_bf16_diff(int r, int shape, int pf);
+StepFn step3d_kernel_f32(int r, int mode, int shape, bool pq);
+StepFn step3d_kernel_f16(int r, int shape, bool pq);
+StepFn step3d_kernel_f16_diff(int r, int shape, bool pq);
+StepFn step3d_kernel_f16_cached(int r, int mode, int shape);
+StepFn step3d_kernel_bf16(int r, int shape, bool pq);
+StepFn step3d_kernel_bf16_diff(int r, int shape, bool pq);
+StepFn step3d_kernel_bf16_cached(int r, int mode, int shape);
 
 namespace {
 
@@ -772,30 +774,38 @@ struct Step3dTable {
     template <int PF>
     static StepFn get(int r, int shape) {
         StepFn f = nullptr;
-        if (shape == 16) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 16, form<Rs, 16>(PF)>, 0) : 0), ...);
-        if (shape == 8) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 8, form<Rs, 8>(PF)>, 0) : 0), ...);
+        if (shape == 16) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 16, PF>, 0) : 0), ...);
+        if (shape == 8) ((r == Rs ? (f = k_step3d<Rs, S, MODE, 8, PF>, 0) : 0), ...);
         // (radii 7 and 8 always run 32 x 32 tiles: no mixed kernel)
-        if (shape == 0) ((r == Rs ? (f = k_step3d<Rs, S, MODE, (Rs <= 6 ? 0 : 8), form<Rs, 0>(PF)>, 0) : 0), ...);
+        if (shape == 0) ((r == Rs ? (f = k_step3d<Rs, S, MODE, (Rs <= 6 ? 0 : 8), PF>, 0) : 0), ...);
         return f;
-    }
-    // kPCached only where it has kernels (at radius 7 and 8 not for 64 x 16
-    // tiles, which the automatic choice never takes there)
-    template <int R, int SHAPE>
-    static constexpr int form(int pf) {
-        const bool split = kSplitP<R, S, MODE> && (SHAPE != 16 || R <= 6);
-        return pf == kPCached && !split ? kPFloat : pf;
     }
 };
 
 // (p codes: kPlain and kDiff only)
 template <Store S, int MODE>
-StepFn step3d_get(int r, int shape, int pf) {
+StepFn step3d_get(int r, int shape, bool pq) {
     using Tb = Step3dTable<S, MODE, 1, 2, 3, 4, 5, 6, 7, 8>;
-    if (pf == kPCodes) {
-        if constexpr (MODE == kPlain || MODE == kDiff) return Tb::template get<kPCodes>(r, shape);
-        return nullptr;
-    }
-    return pf == kPCached ? Tb::template get<kPCached>(r, shape) : Tb::template get<kPFloat>(r, shape);
+    if constexpr (MODE == kPlain || MODE == kDiff)
+        return pq ? Tb::template get<kPCodes>(r, shape) : Tb::template get<kPFloat>(r, shape);
+    else
+        return pq ? nullptr : Tb::template get<kPFloat>(r, shape);
+}
+
+// The kPCached kernels, null where there is none: the radii of kSplitP, and at
+// radius 7 and 8 not for 64 x 16 tiles, which the automatic choice never takes
+// there.
+template <Store S>
+StepFn step3d_get_cached(int r, int mode, int shape) {
+    static_assert(kSplitP<5, S, kPlain> && kSplitP<8, S, kPlain> && kSplitP<6, S, kDiff> && !kSplitP<4, S, kPlain> &&
+                  !kSplitP<7, S, kDiff>);
+    if (mode == kDiff) return Step3dTable<S, kDiff, 5, 6>::template get<kPCached>(r, shape);
+    if (mode != kPlain) return nullptr;
+    if (r <= 6) return Step3dTable<S, kPlain, 5, 6>::template get<kPCached>(r, shape);
+    return shape == 16 ? nullptr
+           : r == 7    ? k_step3d<7, S, kPlain, 8, kPCached>
+           : r == 8    ? k_step3d<8, S, kPlain, 8, kPCached>
+                       : nullptr;
 }
 
 }  // namespace

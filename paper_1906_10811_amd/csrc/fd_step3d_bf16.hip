@@ -6,6 +6,6 @@
 
 namespace fd {
 
-StepFn step3d_kernel_bf16(int r, int shape, int pf) { return step3d_get<Store::BF16, kPlain>(r, shape, pf); }
+StepFn step3d_kernel_bf16(int r, int shape, bool pq) { return step3d_get<Store::BF16, kPlain>(r, shape, pq); }
 
 }  // namespace fd

@@ -7,6 +7,6 @@
 
 namespace fd {
 
-StepFn step3d_kernel_f16_diff(int r, int shape, int pf) { return step3d_get<Store::F16, kDiff>(r, shape, pf); }
+StepFn step3d_kernel_f16_diff(int r, int shape, bool pq) { return step3d_get<Store::F16, kDiff>(r, shape, pq); }
 
 }  // namespace fd

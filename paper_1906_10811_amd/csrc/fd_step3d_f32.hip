@@ -7,12 +7,12 @@
 
 namespace fd {
 
-StepFn step3d_kernel_f32(int r, int mode, int shape, int pf) {
+StepFn step3d_kernel_f32(int r, int mode, int shape, bool pq) {
     switch (mode) {
-        case kPlain: return step3d_get<Store::F32, kPlain>(r, shape, pf);
-        case kBracket: return step3d_get<Store::F32, kBracket>(r, shape, pf);
-        case kImage: return step3d_get<Store::F32, kImage>(r, shape, pf);
-        case kImage3: return step3d_get<Store::F32, kImage3>(r, shape, pf);
+        case kPlain: return step3d_get<Store::F32, kPlain>(r, shape, pq);
+        case kBracket: return step3d_get<Store::F32, kBracket>(r, shape, pq);
+        case kImage: return step3d_get<Store::F32, kImage>(r, shape, pq);
+        case kImage3: return step3d_get<Store::F32, kImage3>(r, shape, pq);
     }
     return nullptr;
 }
